@@ -17,12 +17,12 @@
 // so activations never leave the registers between layers.  The permuted BF16 weights
 // are stored fragment-major ([tile][k-step][lane][8]) and live in LDS.
 #include "fp_closure_dev.h"
+#include "fp_mlp_dev.h"
 
+#include <algorithm>
 #include <mutex>
 #include <string>
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+#include <type_traits>
 
 namespace fpg {
 
@@ -35,27 +35,35 @@ constexpr int IMG_L1 = 0, IMG_L2 = 4096, IMG_L3 = 20480, IMG_L4 = 36864, IMG_BF 
 // FP32 section after the image: b1 b2 b3 b4 x_mean x_std y_mean y_std
 constexpr int SEC_B1 = 0, SEC_B2 = 128, SEC_B3 = 256, SEC_B4 = 384, SEC_XM = 400, SEC_XS = 432,
               SEC_YM = 464, SEC_YS = 480, SEC_N = 496;
-constexpr int TRAIN_CHUNK = 1024;
 
 __device__ __forceinline__ int perm_k(int K) {
     const int s = K >> 4, h = (K >> 3) & 1, i = K & 7;
     return 16 * s + 8 * (i >> 2) + 4 * h + (i & 3);
 }
 
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 // inference: z * sigmoid(z) with the hardware exp2 and reciprocal (about 1 ulp; the
 // result is rounded to bfloat16 right after)
 __device__ __forceinline__ float silu_fast(float z) {
     constexpr float LOG2E = 1.4426950408889634f;
     return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-LOG2E * z));
 }
-__device__ __forceinline__ float dsilu_f(float z) {
-    const float s = 1.0f / (1.0f + __expf(-z));
-    return s * (1.0f + z * (1.0f - s));
+// training: a = silu(z) = z / (1 + e^-z) and its derivative d, both from one exponential and
+// one reciprocal.  The quotients take the steps of a correctly rounded division (reciprocal,
+// one Newton step, two residual corrections) without its scaling of extreme operands: the
+// divisor is at least 1, and beyond 2^126 both results are below 1e-35
+__device__ __forceinline__ float quotient(float x, float d, float r) {
+    float q = x * r;
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, x), r, q);
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, x), r, q);
+    return __builtin_amdgcn_div_fixupf(q, d, x);   // infinities and NaN
 }
-
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+__device__ __forceinline__ void silu_and_derivative(float z, float& a, float& d) {
+    const float u = 1.0f + __expf(-z);
+    float r = __builtin_amdgcn_rcpf(u);
+    r = __builtin_fmaf(__builtin_fmaf(-u, r, 1.0f), r, r);
+    a = quotient(z, u, r);
+    const float s = quotient(1.0f, u, r);
+    d = s * (1.0f + z * (1.0f - s));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -383,233 +391,480 @@ __global__ __launch_bounds__(SENS_BLOCK) void nn_sense_kernel(int32_t ncell, con
 }
 
 // ---------------------------------------------------------------------------------------
-// training kernels (batch along the MFMA columns, activations sample-major in HBM)
+// training: the weights are packed to bfloat16 fragments (forward and transposed), one kernel
+// takes tiles of samples through the forward pass, the loss, the backward pass and the
+// weight gradients, and one kernel adds the workgroups' partial sums (and applies Adam).
+//
+// fragments of 64 lanes x 8 values: F1..F4 the forward A operands (rows = output units), T4
+// T3 T2 the backward ones (rows = input units, inner dimension = output units)
+constexpr int FR_F1 = 0, FR_F2 = 8, FR_F3 = 40, FR_F4 = 72, FR_T4 = 80, FR_T3 = 84, FR_T2 = 116,
+              FR_N = 148;
+// one workgroup's partial gradient: 40 tiles of 32 x 32 in accumulator order (W2 and W3 16
+// each, tile 4 mt + kt; W1 by mt; W4 by kt, its rows 16..31 unused), then b1 b2 b3 b4
+constexpr int GT_W2 = 0, GT_W3 = 16, GT_W1 = 32, GT_W4 = 36, GT_N = 40;
+constexpr int GROW = GT_N * 1024 + 3 * NH + NO;
+constexpr int TRAIN_MAX_WG = 256;   // one workgroup per CU
 
-// H0 = bf16((f - x_mean) / x_std)
-__global__ void nn_input_kernel(int64_t B, const float* __restrict__ feats, const float* __restrict__ p,
-                                __bf16* __restrict__ H0) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= B * NF) return;
-    const int k = (int)(t % NF);
-    H0[t] = (__bf16)((feats[t] - p[OFF_XM + k]) / p[OFF_XS + k]);
+__global__ __launch_bounds__(64) void nn_train_pack_kernel(const float* __restrict__ p, __bf16* __restrict__ img) {
+    const int f = blockIdx.x, lane = threadIdx.x, c = lane & 31, h = lane >> 5;
+    bf16x8 v;
+    if (f < FR_T4) {
+        const bool first = f < FR_F2, last = f >= FR_F4;
+        const int ks = first ? 2 : 8, base = first ? FR_F1 : (f < FR_F3 ? FR_F2 : (last ? FR_F4 : FR_F3));
+        const int off = first ? OFF_W1 : (f < FR_F3 ? OFF_W2 : (last ? OFF_W4 : OFF_W3));
+        const int K = first ? NF : NH, m = ((f - base) / ks) * 32 + c, k0 = ((f - base) % ks) * 16 + 8 * h;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = (__bf16)(last && m >= NO ? 0.0f : p[off + m * K + k0 + i]);
+    } else {
+        const bool last = f < FR_T3;
+        const int ks = last ? 1 : 8, base = last ? FR_T4 : (f < FR_T2 ? FR_T3 : FR_T2);
+        const int off = last ? OFF_W4 : (f < FR_T2 ? OFF_W3 : OFF_W2);
+        const int k = ((f - base) / ks) * 32 + c, m0 = ((f - base) % ks) * 16 + 8 * h;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = (__bf16)p[off + (m0 + i) * NH + k];
+    }
+    *(bf16x8*)(img + (f * 64 + lane) * 8) = v;
 }
 
-// Z[n][m] = sum_k W[m][k] H[n][k] + b[m]; H_out = bf16(silu(Z)) (hidden) or Y = Z (output)
-template <int K, int M, bool ACT>
-__global__ __launch_bounds__(64) void nn_fwd_kernel(int64_t B, const float* __restrict__ W,
-                                                    const float* __restrict__ bias,
-                                                    const __bf16* __restrict__ Hin,
-                                                    float* __restrict__ Z, __bf16* __restrict__ Hout) {
-    constexpr int MT = M >= 32 ? M / 32 : 1, KS = K / 16;
-    const int lane = threadIdx.x, h = lane >> 5, c = lane & 31;
-    const int64_t n = (int64_t)blockIdx.x * 32 + c;
-    const bool valid = n < B;
-    bf16x8 bfr[KS];
+template <int KS>
+__device__ __forceinline__ void load_frags(const __bf16* __restrict__ img, int f0, int lane, bf16x8 (&a)[KS]) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        if (valid) bfr[s] = *(const bf16x8*)(Hin + n * K + 16 * s + 8 * h);
-        else bfr[s] = bf16x8{};
+    for (int s = 0; s < KS; ++s) a[s] = *(const bf16x8*)(img + ((f0 + s) * 64 + lane) * 8);
+}
+
+// D tile of the wave's 32 units and 32 samples: A fragments in registers, B from the
+// sample-major image
+template <int KS>
+__device__ __forceinline__ f32x16 tile_product(const bf16x8 (&a)[KS], const __bf16* hin, int stride, int n, int h) {
+    f32x16 acc = f32x16{};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) acc = mfma32(a[s], *(const bf16x8*)(hin + n * stride + 16 * s + 8 * h), acc);
+    return acc;
+}
+
+// sums over the 32 samples (columns) of the lane's 16 rows of a D tile: every exchange halves
+// the rows a lane keeps; lane l ends with row j = l % 16 of its half (twice: lanes l, l ^ 16)
+__device__ __forceinline__ float row_sums(const float (&v)[16], int lane) {
+    float a[8], b[4], c[2];
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = (b3 ? v[i + 8] : v[i]) + __shfl_xor(b3 ? v[i] : v[i + 8], 8, 64);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = (b2 ? a[i + 4] : a[i]) + __shfl_xor(b2 ? a[i] : a[i + 4], 4, 64);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) c[i] = (b1 ? b[i + 2] : b[i]) + __shfl_xor(b1 ? b[i] : b[i + 2], 2, 64);
+    float s = (b0 ? c[1] : c[0]) + __shfl_xor(b0 ? c[0] : c[1], 1, 64);
+    return s + __shfl_xor(s, 16, 64);
+}
+
+template <int CT, int KIND>
+struct TrainShared {
+    static constexpr int NS = 32 * CT;   // samples of a tile
+    // row strides (bfloat16): 16-byte rows that start on different banks
+    static constexpr int SI = NF + 8, SH = NH + 8, SO = NO + 8, ST = NS + 8;
+    __attribute__((aligned(16))) __bf16 hn[2][NS * SH];    // sample-major: H1 H2 H3, then dZ3 dZ2
+    __attribute__((aligned(16))) __bf16 h0n[NS * SI];
+    __attribute__((aligned(16))) __bf16 h0t[NF * ST];      // unit-major
+    __attribute__((aligned(16))) __bf16 ht[3][NH * ST];    // H1 H2 H3
+    __attribute__((aligned(16))) __bf16 dzt[2][NH * ST];   // dZ3, dZ2, dZ1
+    // KIND 1: the tile's systems wait in dzt, unused until the backward pass, and here
+    static constexpr int SYS_MORE = KIND ? NS * 90 - NH * ST / 2 : 1;
+    double sys_more[SYS_MORE];
+    __attribute__((aligned(16))) __bf16 dyt[NO * ST];      // dY, rows 9..15 zero
+    __attribute__((aligned(16))) __bf16 dyn[NS * SO];
+    float yf[NS * 17];                                     // Y, then dY in columns 0..8
+    float eh[NS];                                          // feature 25, eps_hat
+    __attribute__((aligned(16))) float bias[3 * NH + NO];  // b1 b2 b3 b4
+    __attribute__((aligned(16))) float xm[NF], xs[NF];
+    float ym[NO], ys[NO];
+};
+
+// Forward, loss, backward and weight gradients of B samples, tile by tile.  A workgroup has
+// four waves per 32 samples: wave (ct, rt) computes units 32 rt .. of samples 32 ct .. in
+// every layer.  Activations pass from layer to layer through LDS (sample-major), stay there
+// unit-major for the weight gradients, and the pre-activations' derivatives stay in
+// registers; every wave keeps a tenth (CT = 1) or a twentieth of the weight gradient's 40
+// tiles in accumulators over all of its workgroup's tiles, so that no activation and no
+// back-propagated gradient goes to memory.
+// Bound by the vector work of the activations (about 2200 instructions per wave and tile
+// against 66 MFMA) and, for a single tile, by the chain of nine dependent phases.  A kernel
+// per layer with activations, gradients and FP32 pre-activations in memory, per-lane weight
+// conversions and one thread per bias took 1548 us for an Adam step at batch 4096 and 2658 us
+// at 200,000 (residual loss); this takes 24.5 and 201 us (the kernel itself 21 and 190).
+//   KIND 0: mean over samples of sum_o (y_o - t_o)^2 on standardised targets
+//   KIND 1: mean of |A y - b|^2 of the normalised closure system with y the de-standardised
+//           output (sys[n] = A row-major (81) then b (9), FP64)
+template <int CT, int KIND>
+__global__ __launch_bounds__(256 * CT) void nn_train_kernel(int64_t B, const float* __restrict__ p,
+                                                            const __bf16* __restrict__ img,
+                                                            const float* __restrict__ feats,
+                                                            const float* __restrict__ T,
+                                                            const double* __restrict__ sys,
+                                                            float* __restrict__ part,
+                                                            double* __restrict__ lpart) {
+    using S = TrainShared<CT, KIND>;
+    constexpr int NS = S::NS, BLOCK = 256 * CT, KT = 4 / CT, ITEMS = (NS * 9 + BLOCK - 1) / BLOCK;
+    __shared__ S sm;
+    int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: fragment bases in SGPRs
+    const int rt = wave & 3, ct = wave >> 2;
+    int n = ct * 32 + c;
+    const double invB = 1.0 / (double)B;
+    for (int t = tid; t < NO * S::ST; t += BLOCK) sm.dyt[t] = (__bf16)0.0f;
+    for (int t = tid; t < NS * S::SO; t += BLOCK) sm.dyn[t] = (__bf16)0.0f;
+    for (int t = tid; t < NH; t += BLOCK) {
+        sm.bias[t] = p[OFF_B1 + t];
+        sm.bias[NH + t] = p[OFF_B2 + t];
+        sm.bias[2 * NH + t] = p[OFF_B3 + t];
     }
+    if (tid < NF) {
+        sm.xm[tid] = p[OFF_XM + tid];
+        sm.xs[tid] = p[OFF_XS + tid];
+    }
+    if (tid < NO) {
+        sm.bias[3 * NH + tid] = p[OFF_B4 + tid];
+        sm.ym[tid] = p[OFF_YM + tid];
+        sm.ys[tid] = p[OFF_YS + tid];
+    }
+
+    // this thread's four inputs of a tile: sample tid / 8, features 4 (tid % 8) .. (samples
+    // from B on read the last one's; their output gradients are zero)
+    float fx[4];
+    auto load_inputs = [&](int64_t n0) {
+        const float* f = feats + min(n0 + (tid >> 3), B - 1) * NF + (tid & 7) * 4;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int m = mt * 32 + c;
-        f32x16 acc = f32x16{};
+        for (int e = 0; e < 4; ++e) fx[e] = f[e];
+    };
+    f32x16 g2[KT], g3[KT], gx[2 / CT];   // gx: W1 tile rt and W4 tile rt (CT = 1), else one of them
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            bf16x8 a;
+    for (int t = 0; t < KT; ++t) g2[t] = g3[t] = f32x16{};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = (__bf16)(m < M ? W[m * K + 16 * s + 8 * h + i] : 0.0f);
-            acc = mfma32(a, bfr[s], acc);
-        }
-        if (valid) {
+    for (int t = 0; t < 2 / CT; ++t) gx[t] = f32x16{};
+    float bs[3] = {0.0f, 0.0f, 0.0f};   // bias gradients: the lane's unit row_sums() names
+    float b4 = 0.0f;
+    double loss = 0.0;
+
+    // acc += dZ^T H over the tile's samples: the lane's row of a and column of b (unit-major)
+    auto wgrad = [&](f32x16& acc, const __bf16* a, int row, const __bf16* b, int col) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int mm = mt * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-                if (mm < M) {
-                    const float z = acc[j] + bias[mm];
-                    Z[n * M + mm] = z;
-                    if (ACT) Hout[n * M + mm] = (__bf16)silu_f(z);
-                }
+        for (int s = 0; s < 2 * CT; ++s)
+            acc = mfma32(*(const bf16x8*)(a + row * S::ST + 16 * s + 8 * h),
+                         *(const bf16x8*)(b + col * S::ST + 16 * s + 8 * h), acc);
+    };
+    // hidden layer: activation to both images, derivative kept
+    auto activate = [&](const f32x16& acc, const float* bias, float (&d)[16], __bf16* hs, __bf16* hu) {
+        float a[16];
+#pragma unroll
+        for (int jq = 0; jq < 4; ++jq) {
+            const float4 b = *(const float4*)(bias + rt * 32 + 8 * jq + 4 * h);
+            const float bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float z = acc[4 * jq + e] + bb[e];
+                silu_and_derivative(z, a[4 * jq + e], d[4 * jq + e]);
+                // computed here, not put off to the backward pass with its operands kept
+                __asm__ volatile("" : "+v"(d[4 * jq + e]));
             }
         }
-    }
-}
+        put_tile<true>(hs, S::SH, hu, S::ST, n, rt * 32, h, a);
+    };
+    auto backward = [&](auto inner, const f32x16& acc, const float (&d)[16], float& b, __bf16* zs, __bf16* zu) {
+        float dz[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            dz[j] = acc[j] * d[j];
+        }
+        b += row_sums(dz, lane);
+        put_tile<decltype(inner)::value>(zs, S::SH, zu, S::ST, n, rt * 32, h, dz);
+    };
 
-// loss and dL/dY.  kind 0: mean over samples of sum_o (y_o - t_o)^2 on standardised
-// targets.  kind 1: mean of |A y - b|^2 of the normalised closure system with y the
-// de-standardised output (sys[n] = A row-major (81) then b (9), FP64).
-constexpr int LOSS_BLOCK = 256;
-__global__ __launch_bounds__(LOSS_BLOCK) void nn_loss_kernel(int64_t B, int kind, const float* __restrict__ p,
-                                                              const float* __restrict__ Y,
-                                                              const float* __restrict__ T,
-                                                              const float* __restrict__ feats,
-                                                              const double* __restrict__ sys,
-                                                              float* __restrict__ dY,
-                                                              double* __restrict__ lpart) {
-    __shared__ double sh[LOSS_BLOCK];
-    const int64_t n = (int64_t)blockIdx.x * LOSS_BLOCK + threadIdx.x;
-    double l = 0.0;
-    if (n < B) {
-        const double invB = 1.0 / (double)B;
-        float d[NO];
+    const int64_t tiles = (B + NS - 1) / NS;
+    lds_barrier();
+    load_inputs((int64_t)blockIdx.x * NS);
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t n0 = tile * NS;
+        // the weight fragments are read in every tile: not hoisted out of the loop (they
+        // would not fit in the registers)
+        __asm__ volatile("" ::: "memory");
+        // and neither are the LDS addresses (a register each; spilled, they would be reloaded
+        // one wait at a time): the lane numbers they come from look new in every tile
+        __asm__ volatile("" : "+v"(tid), "+v"(lane), "+v"(h), "+v"(c), "+v"(n));
+        bf16x8 w1[2], w[8], t4[1];
+        load_frags<2>(img, FR_F1 + rt * 2, lane, w1);
+        {
+            const int in_n = tid >> 3, in_k = (tid & 7) * 4;
+            const float4 m4 = *(const float4*)(sm.xm + in_k), s4 = *(const float4*)(sm.xs + in_k);
+            const float xm[4] = {m4.x, m4.y, m4.z, m4.w}, xs[4] = {s4.x, s4.y, s4.z, s4.w};
+            bf16x4 q;
 #pragma unroll
-        for (int o = 0; o < NO; ++o) d[o] = 0.0f;
-        if (kind == 0) {
+            for (int e = 0; e < 4; ++e) {
+                q[e] = (__bf16)((fx[e] - xm[e]) / xs[e]);
+                sm.h0t[(in_k + e) * S::ST + in_n] = q[e];
+            }
+            *(bf16x4*)(sm.h0n + in_n * S::SI + in_k) = q;
+            if (KIND == 1 && in_k == 24) sm.eh[in_n] = fx[1];
+        }
+        // item it of the loss: sample it / 9 of the tile, output it % 9
+        float tv[ITEMS];
+        if constexpr (KIND == 0) {
 #pragma unroll
-            for (int o = 0; o < 9; ++o) {
-                const double t = ((double)T[n * NO + o] - p[OFF_YM + o]) / p[OFF_YS + o];
-                const double e = (double)Y[n * NO + o] - t;
-                l += e * e;
-                d[o] = (float)(2.0 * e * invB);
+            for (int u = 0; u < ITEMS; ++u) {
+                const int it = min(tid + u * BLOCK, NS * 9 - 1), i = it / 9;
+                tv[u] = T[min(n0 + i, B - 1) * NO + (it - 9 * i)];
+            }
+        }
+        // the tile's systems (read once, in order): to LDS while the first layers run
+        constexpr int SQ = KIND ? (NS * 90 + BLOCK - 1) / BLOCK : 1;
+        double sq[SQ];
+        if constexpr (KIND == 1) {
+#pragma unroll
+            for (int u = 0; u < SQ; ++u) sq[u] = sys[min(n0 * 90 + tid + u * BLOCK, B * 90 - 1)];
+        }
+        double* const systems = (double*)sm.dzt[0];   // [sample][90], on into sys_more
+        lds_barrier();
+        float d1[16], d2[16], d3[16];
+        // each layer's fragments are loaded while the layer before it goes through its
+        // activations (some 2000 cycles of vector work)
+        f32x16 acc = tile_product<2>(w1, sm.h0n, S::SI, n, h);
+        load_frags<8>(img, FR_F2 + rt * 8, lane, w);
+        activate(acc, sm.bias, d1, sm.hn[0], sm.ht[0]);
+        lds_barrier();
+        acc = tile_product<8>(w, sm.hn[0], S::SH, n, h);
+        load_frags<8>(img, FR_F3 + rt * 8, lane, w);
+        activate(acc, sm.bias + NH, d2, sm.hn[1], sm.ht[1]);
+        if constexpr (KIND == 1) {
+#pragma unroll
+            for (int u = 0; u < SQ; ++u)
+                if (tid + u * BLOCK < NS * 90) systems[tid + u * BLOCK] = sq[u];
+        }
+        lds_barrier();
+        acc = tile_product<8>(w, sm.hn[1], S::SH, n, h);
+        if (rt == 0) load_frags<8>(img, FR_F4, lane, w);
+        activate(acc, sm.bias + 2 * NH, d3, sm.hn[0], sm.ht[2]);
+        lds_barrier();
+        if (rt == 0) {
+            acc = tile_product<8>(w, sm.hn[0], S::SH, n, h);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int o = 8 * (j >> 2) + 4 * h + (j & 3);
+                sm.yf[n * 17 + o] = acc[j] + sm.bias[3 * NH + o];
+            }
+        }
+        load_frags<1>(img, FR_T4 + rt, lane, t4);
+        load_frags<8>(img, FR_T3 + rt * 8, lane, w);
+        lds_barrier();
+        // loss and dL/dY
+        auto put_dy = [&](int i, int o, float d) {
+            sm.yf[i * 17 + o] = d;
+            sm.dyn[i * S::SO + o] = (__bf16)d;
+            sm.dyt[o * S::ST + i] = (__bf16)d;
+        };
+        if constexpr (KIND == 0) {
+#pragma unroll
+            for (int u = 0; u < ITEMS; ++u) {
+                const int it = tid + u * BLOCK, i = it / 9, o = it - 9 * i;
+                if (it >= NS * 9) continue;
+                float d = 0.0f;
+                if (n0 + i < B) {
+                    const double t = ((double)tv[u] - sm.ym[o]) / sm.ys[o];
+                    const double e = (double)sm.yf[i * 17 + o] - t;
+                    loss += e * e;
+                    d = (float)(2.0 * e * invB);
+                }
+                put_dy(i, o, d);
             }
         } else {
-            const double eh = feats[n * NF + 25];
-            double y[9];
+            // r = A y - b a row per thread, then dL/dy = 2 A^T r a column per thread (a
+            // partial last round only in its waves)
+            double* rr = (double*)sm.hn[1];
 #pragma unroll
-            for (int o = 0; o < 9; ++o) y[o] = (double)Y[n * NO + o] * p[OFF_YS + o] + p[OFF_YM + o];
-            y[0] += 5.0 * eh; y[3] += 5.0 * eh; y[5] += 5.0 * eh;
-            const double* S = sys + n * 90;
-            double r[9];
+            for (int u = 0; u < ITEMS; ++u) {
+                const int it = tid + u * BLOCK, i = it / 9, o = it - 9 * i;
+                if (it >= NS * 9 || n0 + i >= B) continue;
+                const double e5 = 5.0 * (double)sm.eh[i];
+                const double* A = systems + i * 90;
+                double t = -A[81 + o];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                double t = -S[81 + i];
-#pragma unroll
-                for (int k = 0; k < 9; ++k) t = fma(S[i * 9 + k], y[k], t);
-                r[i] = t;
-                l += t * t;
+                for (int k = 0; k < 9; ++k) {
+                    double y = (double)sm.yf[i * 17 + k] * sm.ys[k] + sm.ym[k];
+                    if (k == 0 || k == 3 || k == 5) y += e5;
+                    t = fma(A[o * 9 + k], y, t);
+                }
+                rr[it] = t;
+                loss += t * t;
             }
+            lds_barrier();
 #pragma unroll
-            for (int k = 0; k < 9; ++k) {
-                double g = 0.0;
+            for (int u = 0; u < ITEMS; ++u) {
+                const int it = tid + u * BLOCK, i = it / 9, o = it - 9 * i;
+                if (it >= NS * 9) continue;
+                float d = 0.0f;
+                if (n0 + i < B) {
+                    const double* A = systems + i * 90;
+                    double g = 0.0;
 #pragma unroll
-                for (int i = 0; i < 9; ++i) g = fma(S[i * 9 + k], r[i], g);
-                d[k] = (float)(2.0 * g * invB * p[OFF_YS + k]);
+                    for (int k = 0; k < 9; ++k) g = fma(A[k * 9 + o], rr[9 * i + k], g);
+                    d = (float)(2.0 * g * invB * sm.ys[o]);
+                }
+                put_dy(i, o, d);
             }
         }
+        lds_barrier();
+        backward(std::true_type{}, tile_product<1>(t4, sm.dyn, S::SO, n, h), d3, bs[2], sm.hn[1], sm.dzt[0]);
+        if (wave == 0) {
+            // the output bias: lane = output + 16 x quarter of the tile's samples
 #pragma unroll
-        for (int o = 0; o < NO; ++o) dY[n * NO + o] = d[o];
+            for (int i = 0; i < NS / 4; ++i) b4 += sm.yf[((lane >> 4) * (NS / 4) + i) * 17 + (lane & 15)];
+        }
+        load_inputs((tile + gridDim.x) * NS);
+        lds_barrier();
+        acc = tile_product<8>(w, sm.hn[1], S::SH, n, h);
+        load_frags<8>(img, FR_T2 + rt * 8, lane, w);
+        backward(std::true_type{}, acc, d2, bs[1], sm.hn[0], sm.dzt[1]);
+        if (CT == 1 || ct == 1) wgrad(gx[2 / CT - 1], sm.dyt, c & 15, sm.ht[2], rt * 32 + c);
+#pragma unroll
+        for (int t = 0; t < KT; ++t) wgrad(g3[t], sm.dzt[0], rt * 32 + c, sm.ht[1], (ct * KT + t) * 32 + c);
+        lds_barrier();
+        backward(std::false_type{}, tile_product<8>(w, sm.hn[0], S::SH, n, h), d1, bs[0], (__bf16*)nullptr, sm.dzt[0]);
+#pragma unroll
+        for (int t = 0; t < KT; ++t) wgrad(g2[t], sm.dzt[1], rt * 32 + c, sm.ht[0], (ct * KT + t) * 32 + c);
+        lds_barrier();
+        if (CT == 1 || ct == 0) wgrad(gx[0], sm.dzt[0], rt * 32 + c, sm.h0t, c);
+        lds_barrier();
     }
-    sh[threadIdx.x] = l;
-    __syncthreads();
-    for (int s = LOSS_BLOCK / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+
+    float* out = part + (int64_t)blockIdx.x * GROW;
+    auto put_tile = [&](int t, const f32x16& g) {
+#pragma unroll
+        for (int jq = 0; jq < 4; ++jq)
+            *(float4*)(out + t * 1024 + jq * 256 + lane * 4) =
+                make_float4(g[4 * jq], g[4 * jq + 1], g[4 * jq + 2], g[4 * jq + 3]);
+    };
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+        put_tile(GT_W2 + rt * 4 + ct * KT + t, g2[t]);
+        put_tile(GT_W3 + rt * 4 + ct * KT + t, g3[t]);
     }
-    if (threadIdx.x == 0) lpart[blockIdx.x] = sh[0];
+    if (CT == 1) {
+        put_tile(GT_W1 + rt, gx[0]);
+        put_tile(GT_W4 + rt, gx[2 / CT - 1]);
+    } else {
+        put_tile((ct == 0 ? GT_W1 : GT_W4) + rt, gx[0]);
+    }
+    // biases: over the wave's 32 samples, then the waves of the same units; loss: over all
+    float* bl = sm.yf;
+    if (!(lane & 16)) {
+        const int j = lane & 15;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) bl[ct * 3 * NH + l * NH + rt * 32 + 8 * (j >> 2) + 4 * h + (j & 3)] = bs[l];
+    }
+    double* ll = (double*)sm.dzt[1];
+    ll[tid] = loss;
+    b4 += __shfl_xor(b4, 16, 64);
+    b4 += __shfl_xor(b4, 32, 64);
+    lds_barrier();
+    for (int t = tid; t < 3 * NH; t += BLOCK) out[GT_N * 1024 + t] = CT == 1 ? bl[t] : bl[t] + bl[3 * NH + t];
+    if (tid < NO) out[GT_N * 1024 + 3 * NH + tid] = tid < 9 ? b4 : 0.0f;
+    for (int s = BLOCK / 2; s > 0; s >>= 1) {
+        if (tid < s) ll[tid] += ll[tid + s];
+        lds_barrier();
+    }
+    if (tid == 0) lpart[blockIdx.x] = ll[0];
 }
 
-__global__ void nn_loss_final_kernel(int nb, int64_t B, const double* __restrict__ lpart,
-                                     float* __restrict__ loss) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+// Adam (Kingma and Ba) on one trainable parameter, FP32 master weights
+struct AdamArgs {
+    float *p, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+};
+__device__ __forceinline__ void adam_one(const AdamArgs& a, int64_t q, float gq, float mq, float vq, float pq) {
+    mq = a.b1 * mq + (1.0f - a.b1) * gq;
+    vq = a.b2 * vq + (1.0f - a.b2) * gq * gq;
+    a.m[q] = mq;
+    a.v[q] = vq;
+    a.p[q] = pq - a.lr * (mq / a.c1) / (sqrtf(vq / a.c2) + a.eps);
+}
+
+// grad = the workgroups' partial sums added in order (16 ranges of rows by 16 waves, then the
+// ranges), a float4 of four values per lane; with ADAM the parameters are updated as well.
+// The last workgroup adds the loss.
+constexpr int RED_R = 16, RED_BLOCK = 64 * RED_R;
+template <bool ADAM>
+__global__ __launch_bounds__(RED_BLOCK) void nn_reduce_kernel(int rows, const float* __restrict__ part,
+                                                              const double* __restrict__ lpart, int64_t B,
+                                                              float* __restrict__ grad, float* __restrict__ loss,
+                                                              AdamArgs ad) {
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x >= 64) return;
         double s = 0.0;
-        for (int i = 0; i < nb; ++i) s += lpart[i];
-        *loss = (float)(s / (double)B);
+        for (int i = lane; i < rows; i += 64) s += lpart[i];
+        s = group_sum<64>(s);
+        if (lane == 0) *loss = (float)(s / (double)B);
+        return;
     }
-}
-
-// dH[n][k] = sum_m dZ[n][m] W[m][k];  out[n][k] = dH * silu'(Zprev[n][k])
-template <int M, int K>
-__global__ __launch_bounds__(64) void nn_bwd_kernel(int64_t B, const float* __restrict__ W,
-                                                    const float* __restrict__ dZ,
-                                                    const float* __restrict__ Zprev,
-                                                    float* __restrict__ dZprev) {
-    constexpr int KT = K / 32, MS = M / 16;
-    const int lane = threadIdx.x, h = lane >> 5, c = lane & 31;
-    const int64_t n = (int64_t)blockIdx.x * 32 + c;
-    const bool valid = n < B;
-    bf16x8 bfr[MS];
-#pragma unroll
-    for (int s = 0; s < MS; ++s)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) bfr[s][i] = (__bf16)(valid ? dZ[n * M + 16 * s + 8 * h + i] : 0.0f);
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-        const int k = kt * 32 + c;
-        f32x16 acc = f32x16{};
-#pragma unroll
-        for (int s = 0; s < MS; ++s) {
-            bf16x8 a;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = (__bf16)W[(16 * s + 8 * h + i) * K + k];
-            acc = mfma32(a, bfr[s], acc);
+    __shared__ float4 red[RED_R][64];
+    const int f4 = blockIdx.x * 64 + lane;
+    const bool in = f4 < GROW / 4;
+    // parameter of the lane's first value, the stride to the next ones, and whether they exist
+    int q, st = 1;
+    bool live = in;
+    if (f4 < GT_N * 256) {
+        const int t = f4 >> 8, row = 8 * ((f4 >> 6) & 3) + 4 * (lane >> 5), col = lane & 31;
+        st = NH;
+        if (t < GT_W1) q = (t < GT_W3 ? OFF_W2 : OFF_W3) + (((t & 15) >> 2) * 32 + row) * NH + (t & 3) * 32 + col;
+        else if (t < GT_W4) q = OFF_W1 + ((t - GT_W1) * 32 + row) * (st = NF) + col;
+        else {
+            q = OFF_W4 + row * NH + (t - GT_W4) * 32 + col;
+            live = row < NO;
         }
-        if (valid) {
+    } else {
+        const int i = (f4 - GT_N * 256) * 4;
+        q = i < NH ? OFF_B1 + i : (i < 2 * NH ? OFF_B2 + i - NH : (i < 3 * NH ? OFF_B3 + i - 2 * NH : OFF_B4 + i - 3 * NH));
+    }
+    float pq[4], mq[4], vq[4];
+    if (ADAM && r == 0 && live) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int kk = kt * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-                dZprev[n * K + kk] = acc[j] * dsilu_f(Zprev[n * K + kk]);
-            }
+        for (int e = 0; e < 4; ++e) {
+            pq[e] = ad.p[q + e * st];
+            mq[e] = ad.m[q + e * st];
+            vq[e] = ad.v[q + e * st];
         }
     }
-}
-
-// partial weight gradient of one chunk of samples: dWp[chunk][m][k] = sum_n dZ[n][m] H[n][k]
-template <int M, int K>
-__global__ __launch_bounds__(64) void nn_wgrad_kernel(int64_t B, const float* __restrict__ dZ,
-                                                      const __bf16* __restrict__ H,
-                                                      float* __restrict__ part, int64_t pstride,
-                                                      int woff) {
-    constexpr int MT = M >= 32 ? M / 32 : 1, KT = K / 32;
-    const int lane = threadIdx.x, h = lane >> 5, c = lane & 31;
-    const int chunk = blockIdx.y;
-    const int mt = blockIdx.x / KT, kt = blockIdx.x % KT;
-    const int m = mt * 32 + c, k = kt * 32 + c;
-    const int64_t n0 = (int64_t)chunk * TRAIN_CHUNK;
-    f32x16 acc = f32x16{};
-    for (int s = 0; s < TRAIN_CHUNK / 16; ++s) {
-        bf16x8 a, b;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int64_t n = n0 + 16 * s + 8 * h + i;
-            const bool v = n < B;
-            a[i] = (__bf16)((v && m < M) ? dZ[n * M + m] : 0.0f);
-            b[i] = v ? H[n * K + k] : (__bf16)0.0f;
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (in) {
+        const int r1 = (r + 1) * rows / RED_R;
+#pragma unroll 8
+        for (int i = r * rows / RED_R; i < r1; ++i) {
+            const float4 v = *(const float4*)(part + (int64_t)i * GROW + f4 * 4);
+            s.x += v.x;
+            s.y += v.y;
+            s.z += v.z;
+            s.w += v.w;
         }
-        acc = mfma32(a, b, acc);
     }
-    float* dst = part + (int64_t)chunk * pstride + woff;
+    red[r][lane] = s;
+    __syncthreads();
+    if (r != 0 || !live) return;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int mm = mt * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-        if (mm < M) dst[mm * K + k] = acc[j];
+    for (int i = 1; i < RED_R; ++i) {
+        const float4 v = red[i][lane];
+        s.x += v.x;
+        s.y += v.y;
+        s.z += v.z;
+        s.w += v.w;
+    }
+    const float g[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        grad[q + e * st] = g[e];
+        if (ADAM) adam_one(ad, q + e * st, g[e], mq[e], vq[e], pq[e]);
     }
 }
 
-// partial bias gradient of one chunk: dbp[chunk][m] = sum_n dZ[n][m] (sequential, FP32)
-__global__ void nn_bgrad_kernel(int64_t B, int M, const float* __restrict__ dZ,
-                                float* __restrict__ part, int64_t pstride, int boff) {
-    const int m = threadIdx.x;
-    const int chunk = blockIdx.x;
-    if (m >= M) return;
-    const int64_t n0 = (int64_t)chunk * TRAIN_CHUNK;
-    const int64_t n1 = n0 + TRAIN_CHUNK < B ? n0 + TRAIN_CHUNK : B;
-    float s = 0.0f;
-    for (int64_t n = n0; n < n1; ++n) s += dZ[n * M + m];
-    part[(int64_t)chunk * pstride + boff + m] = s;
-}
-
-// grad[q] = sum over chunks in order of part[chunk][q]
-__global__ void nn_reduce_kernel(int nchunk, const float* __restrict__ part, int64_t pstride,
-                                 float* __restrict__ grad) {
+__global__ void nn_adam_kernel(AdamArgs a, const float* __restrict__ g) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N_TRAIN) return;
-    float s = 0.0f;
-    for (int c = 0; c < nchunk; ++c) s += part[(int64_t)c * pstride + q];
-    grad[q] = s;
-}
-
-// Adam (Kingma and Ba) on the trainable prefix, FP32 master weights
-__global__ void nn_adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                               float* __restrict__ v, float lr, float b1, float b2, float eps,
-                               float c1, float c2) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N_TRAIN) return;
-    const float gq = g[q];
-    const float mq = b1 * m[q] + (1.0f - b1) * gq;
-    const float vq = b2 * v[q] + (1.0f - b2) * gq * gq;
-    m[q] = mq;
-    v[q] = vq;
-    p[q] -= lr * (mq / c1) / (sqrtf(vq / c2) + eps);
+    if (q < N_TRAIN) adam_one(a, q, g[q], a.m[q], a.v[q], a.p[q]);
 }
 
 // features of a batch of moment records (raw, unstandardised) for training
@@ -672,12 +927,10 @@ struct fp_nn {
     __bf16* img = nullptr;
     float* sec = nullptr;
     float* ybuf = nullptr;   // [ncell][16] standardised outputs of the last inference
-    // training scratch
-    __bf16 *H0 = nullptr, *H1 = nullptr, *H2 = nullptr, *H3 = nullptr;
-    float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr, *Y = nullptr, *dY = nullptr;
-    float *dZa = nullptr, *dZb = nullptr, *part = nullptr, *grad = nullptr;
+    // training scratch: weight fragments, partial gradients and losses of the workgroups
+    __bf16* timg = nullptr;
+    float *part = nullptr, *grad = nullptr;
     double* lpart = nullptr;
-    int nchunk = 0;
 };
 
 template <typename T>
@@ -729,16 +982,12 @@ extern "C" int fp_nn_create(fp_ctx* c, int64_t max_batch, fp_nn** out) {
     if (!n) return FP_ENOMEM;
     n->ctx = c;
     n->max_batch = max_batch;
-    const size_t B = (size_t)max_batch;
-    n->nchunk = (int)((max_batch + TRAIN_CHUNK - 1) / TRAIN_CHUNK);
+    // the most workgroups of any batch up to max_batch
+    const size_t rows = (size_t)std::min<int64_t>(TRAIN_MAX_WG, (max_batch + 31) / 32);
     bool ok = nalloc(&n->img, IMG_BF) && nalloc(&n->sec, SEC_N) && nalloc(&n->ybuf, (size_t)c->ncell * NO);
-    if (ok && B > 0)
-        ok = nalloc(&n->H0, B * NF) && nalloc(&n->H1, B * NH) && nalloc(&n->H2, B * NH) &&
-             nalloc(&n->H3, B * NH) && nalloc(&n->Z1, B * NH) && nalloc(&n->Z2, B * NH) &&
-             nalloc(&n->Z3, B * NH) && nalloc(&n->Y, B * NO) && nalloc(&n->dY, B * NO) &&
-             nalloc(&n->dZa, B * NH) && nalloc(&n->dZb, B * NH) &&
-             nalloc(&n->part, (size_t)n->nchunk * N_TRAIN) && nalloc(&n->grad, N_PARAMS) &&
-             nalloc(&n->lpart, B / LOSS_BLOCK + 1);
+    if (ok && max_batch > 0)
+        ok = nalloc(&n->timg, FR_N * 512) && nalloc(&n->part, rows * GROW) && nalloc(&n->grad, N_PARAMS) &&
+             nalloc(&n->lpart, rows);
     if (!ok) {
         fp_nn_destroy(n);
         return FP_ENOMEM;
@@ -750,10 +999,8 @@ extern "C" int fp_nn_create(fp_ctx* c, int64_t max_batch, fp_nn** out) {
 extern "C" void fp_nn_destroy(fp_nn* n) {
     if (!n) return;
     (void)hipDeviceSynchronize();
-    for (void* p : {(void*)n->img, (void*)n->sec, (void*)n->ybuf, (void*)n->H0, (void*)n->H1,
-                    (void*)n->H2, (void*)n->H3, (void*)n->Z1, (void*)n->Z2, (void*)n->Z3,
-                    (void*)n->Y, (void*)n->dY, (void*)n->dZa, (void*)n->dZb, (void*)n->part,
-                    (void*)n->grad, (void*)n->lpart})
+    for (void* p : {(void*)n->img, (void*)n->sec, (void*)n->ybuf, (void*)n->timg, (void*)n->part, (void*)n->grad,
+                    (void*)n->lpart})
         (void)hipFree(p);
     delete n;
 }
@@ -867,65 +1114,58 @@ extern "C" int fp_closure_build(fp_ctx* c, const double* mom, int64_t n, double*
     return check_launch(c, "fp_closure_build");
 }
 
+// gradient (and, with ad, the Adam step on it); the arguments are checked
+static int train_launch(fp_ctx* c, fp_nn* n, const float* params, const float* feats, const float* targets,
+                        const double* sys, int64_t B, int32_t loss_kind, float* grad, float* loss,
+                        const AdamArgs* ad, const char* what, hipStream_t s) {
+    hipLaunchKernelGGL(nn_train_pack_kernel, dim3(FR_N), dim3(64), 0, s, params, n->timg);
+    // tiles of 32 samples while they fit on the CUs at once (the shorter chain per workgroup),
+    // else of 64, a workgroup per CU: eight waves hide each other's latencies, and the
+    // partial gradients (165 KB a workgroup, written and read back) grow no further.  Just
+    // below and above the line: 38.7 us at 8192 samples, 40.8 us at 16,384
+    const bool small = B <= 32 * TRAIN_MAX_WG;
+    const int rows = small ? (int)((B + 31) / 32) : (int)std::min<int64_t>(TRAIN_MAX_WG, (B + 63) / 64);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(small ? 256 : 512), 0, s, B, params, (const __bf16*)n->timg, feats,
+                           targets, sys, n->part, n->lpart);
+    };
+    if (loss_kind == 0) launch(small ? nn_train_kernel<1, 0> : nn_train_kernel<2, 0>);
+    else launch(small ? nn_train_kernel<1, 1> : nn_train_kernel<2, 1>);
+    const dim3 rgrid((GROW / 4 + 63) / 64 + 1);
+    if (ad)
+        hipLaunchKernelGGL(nn_reduce_kernel<true>, rgrid, dim3(RED_BLOCK), 0, s, rows, (const float*)n->part,
+                           (const double*)n->lpart, B, grad, loss, *ad);
+    else
+        hipLaunchKernelGGL(nn_reduce_kernel<false>, rgrid, dim3(RED_BLOCK), 0, s, rows, (const float*)n->part,
+                           (const double*)n->lpart, B, grad, loss, AdamArgs{});
+    return check_launch(c, what);
+}
+
+static bool grad_args(const fp_ctx* c, const fp_nn* n, const float* params, const float* feats, const float* targets,
+                      const double* sys, int64_t B, int32_t loss_kind, const float* grad, const float* loss) {
+    return c && n && params && feats && grad && loss && B > 0 && B <= n->max_batch &&
+           (loss_kind == 0 || loss_kind == 1) && (loss_kind != 0 || targets) && (loss_kind != 1 || sys);
+}
+
+static AdamArgs adam_args(float* params, float* m, float* v, int64_t t, float lr) {
+    return {params, m, v, lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - pow(0.9, (double)t)),
+            (float)(1.0 - pow(0.999, (double)t))};
+}
+
 extern "C" int fp_nn_grad(fp_ctx* c, fp_nn* n, const float* params, const float* feats,
                           const float* targets, const double* sys, int64_t B, int32_t loss_kind,
                           float* grad, float* loss, hipStream_t s) {
-    if (!c || !n || !params || !feats || !grad || !loss || B <= 0 || B > n->max_batch ||
-        (loss_kind != 0 && loss_kind != 1) || (loss_kind == 0 && !targets) ||
-        (loss_kind == 1 && !sys))
+    if (!grad_args(c, n, params, feats, targets, sys, B, loss_kind, grad, loss))
         return set_err(c, FP_EINVAL, "fp_nn_grad: bad argument");
-    const unsigned g32 = (unsigned)((B + 31) / 32);
-    const int nchunk = (int)((B + TRAIN_CHUNK - 1) / TRAIN_CHUNK);
-    hipLaunchKernelGGL(nn_input_kernel, dim3((unsigned)((B * NF + 255) / 256)), dim3(256), 0, s, B,
-                       feats, params, n->H0);
-    hipLaunchKernelGGL((nn_fwd_kernel<NF, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W1,
-                       params + OFF_B1, n->H0, n->Z1, n->H1);
-    hipLaunchKernelGGL((nn_fwd_kernel<NH, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W2,
-                       params + OFF_B2, n->H1, n->Z2, n->H2);
-    hipLaunchKernelGGL((nn_fwd_kernel<NH, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W3,
-                       params + OFF_B3, n->H2, n->Z3, n->H3);
-    hipLaunchKernelGGL((nn_fwd_kernel<NH, NO, false>), dim3(g32), dim3(64), 0, s, B, params + OFF_W4,
-                       params + OFF_B4, n->H3, n->Y, (__bf16*)nullptr);
-    const int nb = (int)((B + LOSS_BLOCK - 1) / LOSS_BLOCK);
-    hipLaunchKernelGGL(nn_loss_kernel, dim3(nb), dim3(LOSS_BLOCK), 0, s, B, (int)loss_kind, params,
-                       n->Y, targets, feats, sys, n->dY, n->lpart);
-    hipLaunchKernelGGL(nn_loss_final_kernel, dim3(1), dim3(64), 0, s, nb, B, n->lpart, loss);
-    const int64_t ps = N_TRAIN;
-    // layer 4: dZ4 = dY
-    hipLaunchKernelGGL((nn_wgrad_kernel<NO, NH>), dim3(1 * (NH / 32), nchunk), dim3(64), 0, s, B, n->dY,
-                       n->H3, n->part, ps, OFF_W4);
-    hipLaunchKernelGGL(nn_bgrad_kernel, dim3(nchunk), dim3(128), 0, s, B, NO, n->dY, n->part, ps, OFF_B4);
-    hipLaunchKernelGGL((nn_bwd_kernel<NO, NH>), dim3(g32), dim3(64), 0, s, B, params + OFF_W4, n->dY,
-                       n->Z3, n->dZa);
-    // layer 3
-    hipLaunchKernelGGL((nn_wgrad_kernel<NH, NH>), dim3(16, nchunk), dim3(64), 0, s, B, n->dZa, n->H2,
-                       n->part, ps, OFF_W3);
-    hipLaunchKernelGGL(nn_bgrad_kernel, dim3(nchunk), dim3(128), 0, s, B, NH, n->dZa, n->part, ps, OFF_B3);
-    hipLaunchKernelGGL((nn_bwd_kernel<NH, NH>), dim3(g32), dim3(64), 0, s, B, params + OFF_W3, n->dZa,
-                       n->Z2, n->dZb);
-    // layer 2
-    hipLaunchKernelGGL((nn_wgrad_kernel<NH, NH>), dim3(16, nchunk), dim3(64), 0, s, B, n->dZb, n->H1,
-                       n->part, ps, OFF_W2);
-    hipLaunchKernelGGL(nn_bgrad_kernel, dim3(nchunk), dim3(128), 0, s, B, NH, n->dZb, n->part, ps, OFF_B2);
-    hipLaunchKernelGGL((nn_bwd_kernel<NH, NH>), dim3(g32), dim3(64), 0, s, B, params + OFF_W2, n->dZb,
-                       n->Z1, n->dZa);
-    // layer 1
-    hipLaunchKernelGGL((nn_wgrad_kernel<NH, NF>), dim3(4, nchunk), dim3(64), 0, s, B, n->dZa, n->H0,
-                       n->part, ps, OFF_W1);
-    hipLaunchKernelGGL(nn_bgrad_kernel, dim3(nchunk), dim3(128), 0, s, B, NH, n->dZa, n->part, ps, OFF_B1);
-    hipLaunchKernelGGL(nn_reduce_kernel, dim3((N_TRAIN + 255) / 256), dim3(256), 0, s, nchunk, n->part,
-                       ps, grad);
-    return check_launch(c, "fp_nn_grad");
+    return train_launch(c, n, params, feats, targets, sys, B, loss_kind, grad, loss, nullptr, "fp_nn_grad", s);
 }
 
 extern "C" int fp_nn_adam(fp_ctx* c, float* params, const float* grad, float* m, float* v,
                           int64_t t, float lr, hipStream_t s) {
     if (!c || !params || !grad || !m || !v || t < 1 || !(lr >= 0.0f))
         return set_err(c, FP_EINVAL, "fp_nn_adam: bad argument");
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = (float)(1.0 - pow(0.9, (double)t)), c2 = (float)(1.0 - pow(0.999, (double)t));
-    hipLaunchKernelGGL(nn_adam_kernel, dim3((N_TRAIN + 255) / 256), dim3(256), 0, s, params, grad, m, v,
-                       lr, b1, b2, eps, c1, c2);
+    hipLaunchKernelGGL(nn_adam_kernel, dim3((N_TRAIN + 255) / 256), dim3(256), 0, s, adam_args(params, m, v, t, lr),
+                       grad);
     return check_launch(c, "fp_nn_adam");
 }
 
@@ -933,7 +1173,14 @@ extern "C" int fp_nn_train_step(fp_ctx* c, fp_nn* n, float* params, float* m, fl
                                 float lr, const float* feats, const float* targets, const double* sys,
                                 int64_t B, int32_t loss_kind, float* loss, hipStream_t s) {
     if (!n) return set_err(c, FP_EINVAL, "fp_nn_train_step: bad argument");
-    int rc = fp_nn_grad(c, n, params, feats, targets, sys, B, loss_kind, n->grad, loss, s);
-    if (rc) return rc;
-    return fp_nn_adam(c, params, n->grad, m, v, t, lr, s);
+    if (!grad_args(c, n, params, feats, targets, sys, B, loss_kind, n->grad, loss))
+        return set_err(c, FP_EINVAL, "fp_nn_grad: bad argument");
+    if (!m || !v || t < 1 || !(lr >= 0.0f)) {
+        // as the two calls would: the gradient and the loss, then the refusal
+        const int rc = train_launch(c, n, params, feats, targets, sys, B, loss_kind, n->grad, loss, nullptr,
+                                    "fp_nn_grad", s);
+        return rc ? rc : set_err(c, FP_EINVAL, "fp_nn_adam: bad argument");
+    }
+    const AdamArgs ad = adam_args(params, m, v, t, lr);
+    return train_launch(c, n, params, feats, targets, sys, B, loss_kind, n->grad, loss, &ad, "fp_nn_train_step", s);
 }
