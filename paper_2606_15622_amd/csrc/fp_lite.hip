@@ -15,13 +15,12 @@
 // DM2 = <|c|^2>, nu = 1/tau; targets Ct (6) and Gamma (3) of the update record, in solver
 // units, standardised.
 #include "fp_closure_dev.h"
+#include "fp_mlp_dev.h"
 
+#include <algorithm>
 #include <cmath>
 #include <new>
 #include <string>
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace fpg {
 namespace lite {
@@ -41,18 +40,14 @@ constexpr int IMG_L1 = 0, IMG_L2 = 4096, IMG_L3 = 69632, IMG_L4 = 135168, IMG_L5
 // check kernel, which receives normalised coefficients
 constexpr int SEC_B1 = 0, SEC_B2 = 256, SEC_B3 = 512, SEC_B4 = 768, SEC_B5 = 1024, SEC_XM = 1040,
               SEC_XS = 1056, SEC_YM = 1072, SEC_YS = 1088, SEC_ID = 1104, SEC_N = 1136;
-constexpr int TRAIN_CHUNK = 1024;
 constexpr int INF_BLOCK = 512;                  // 8 waves, 256 cells per workgroup
 constexpr int LDS_BF = NT * KS * 512;           // one hidden layer: 65536 BF16 (128 KB)
 
 static_assert(IMG_L2 - IMG_L1 == NT * 512 && IMG_L3 - IMG_L2 == LDS_BF && IMG_L5 - IMG_L4 == LDS_BF &&
                   IMG_BF - IMG_L5 == KS * 512,
               "image layout");
+static_assert(OFF_B3 - OFF_B2 == OFF_B2 - OFF_B1 && OFF_B4 - OFF_B3 == OFF_B2 - OFF_B1, "parameter layout");
 static_assert(OFF_B5 + NO == N_TRAIN && OFF_YS + NO == N_PARAMS, "parameter layout");
-
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
 
 // k-slot K of a hidden layer's input holds activation row perm_k(K) of the previous layer
 __device__ __forceinline__ int perm_k(int K) {
@@ -261,200 +256,467 @@ __global__ __launch_bounds__(INF_BLOCK) void lite_infer_kernel(fp_config g, int3
 }
 
 // ---------------------------------------------------------------------------------------
-// training (batch along the MFMA columns, activations sample-major in HBM)
+// training: the weights are packed to bfloat16 fragments (forward and transposed); one kernel
+// takes tiles of samples through the forward pass, the loss and the backward pass, and leaves
+// every layer's activations and pre-activation gradients as bfloat16 fragments whose inner
+// dimension is the sample; one kernel multiplies those into the weight gradients, split over
+// the samples; one adds the splits (and applies Adam).
+//
+// fragments of 64 lanes x 8 values: F1..F5 the forward A operands (rows = output units),
+// T5..T2 the backward ones (rows = input units, inner dimension = output units)
+constexpr int FR_F1 = 0, FR_F2 = NT, FR_F5 = FR_F2 + 3 * NT * KS, FR_T5 = FR_F5 + KS, FR_T2 = FR_T5 + NT,
+              FR_N = FR_T2 + 3 * NT * KS;
+// fragments of one 16-sample group: H1..H4 and dZ1..dZ4 (NT each), H0, dY (units 16..31 are
+// copies of 0..15, their products are not used)
+constexpr int SF_H = 0, SF_Z = 4 * NT, SF_H0 = 8 * NT, SF_DY = 8 * NT + 1, SF_N = 8 * NT + 2;
+// one split's weight gradient: tiles of 32 x 32 in accumulator order, W2 W3 W4 (NT x NT each),
+// W1 (by unit tile), W5 (by input tile, its rows 16..31 unused)
+constexpr int GT_W1 = 3 * NT * NT, GT_W5 = GT_W1 + NT, GT_N = GT_W5 + NT;
+constexpr int BROW = 4 * NH + NO;         // bias gradients of one workgroup: b1 .. b5
+constexpr int TRAIN_MAX_WG = 256;         // one workgroup per CU
+// splits of the weight gradients: 16 sample groups (256 samples) each while that gives at
+// most 32
+constexpr int SPLIT_GROUPS = 16, MAX_SPLITS = 32;
 
-__global__ void lite_input_kernel(int64_t B, const float* __restrict__ feats, const float* __restrict__ p,
-                                  __bf16* __restrict__ H0) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= B * NF) return;
-    const int k = (int)(t % NF);
-    H0[t] = (__bf16)((feats[t] - p[OFF_XM + k]) / p[OFF_XS + k]);
+__host__ __device__ constexpr int64_t off_w(int layer) {   // layer 1..5
+    return layer == 1 ? OFF_W1 : (layer == 5 ? OFF_W5 : OFF_W2 + (layer - 2) * (OFF_W3 - OFF_W2));
 }
 
-// Z[n][m] = sum_k W[m][k] H[n][k] + b[m]; H_out = bf16(relu(Z)) (hidden) or Y = Z (output)
-template <int K, int M, bool ACT>
-__global__ __launch_bounds__(64) void lite_fwd_kernel(int64_t B, const float* __restrict__ W,
-                                                      const float* __restrict__ bias,
-                                                      const __bf16* __restrict__ Hin,
-                                                      float* __restrict__ Z, __bf16* __restrict__ Hout) {
-    constexpr int MT = M >= 32 ? M / 32 : 1, KSN = K / 16;
-    const int lane = threadIdx.x, h = lane >> 5, c = lane & 31;
-    const int64_t n = (int64_t)blockIdx.x * 32 + c;
-    const bool valid = n < B;
-    bf16x8 bfr[KSN];
+__global__ __launch_bounds__(64) void lite_train_pack_kernel(const float* __restrict__ p, __bf16* __restrict__ img) {
+    const int f = blockIdx.x, lane = threadIdx.x, c = lane & 31, h = lane >> 5;
+    bf16x8 v;
+    if (f < FR_T5) {
+        const bool first = f < FR_F2, last = f >= FR_F5;
+        const int e = first ? f : (last ? f - FR_F5 : (f - FR_F2) % (NT * KS)), ks = first ? 1 : KS;
+        const int layer = first ? 1 : (last ? 5 : 2 + (f - FR_F2) / (NT * KS));
+        const int K = first ? NF : NH, m = (e / ks) * 32 + c, k0 = (e % ks) * 16 + 8 * h;
 #pragma unroll
-    for (int s = 0; s < KSN; ++s) {
-        if (valid) bfr[s] = *(const bf16x8*)(Hin + n * K + 16 * s + 8 * h);
-        else bfr[s] = bf16x8{};
+        for (int i = 0; i < 8; ++i) v[i] = (__bf16)(last && m >= NO ? 0.0f : p[off_w(layer) + m * K + k0 + i]);
+    } else {
+        const bool last = f < FR_T2;
+        const int e = last ? f - FR_T5 : (f - FR_T2) % (NT * KS), ks = last ? 1 : KS;
+        const int layer = last ? 5 : 2 + (f - FR_T2) / (NT * KS);
+        const int k = (e / ks) * 32 + c, m0 = (e % ks) * 16 + 8 * h;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = (__bf16)p[off_w(layer) + (m0 + i) * NH + k];
     }
-    for (int mt = 0; mt < MT; ++mt) {
-        const int m = mt * 32 + c;
-        f32x16 acc = f32x16{};
+    *(bf16x8*)(img + (f * 64 + lane) * 8) = v;
+}
+
+template <int CT>
+struct TrainShared {
+    static constexpr int NS = 32 * CT;   // samples of a tile
+    // row strides (bfloat16): 16-byte rows that start on different banks
+    static constexpr int SH = NH + 8, SI = NF + 8, ST = NS + 8, SP = 40;
+    __attribute__((aligned(16))) __bf16 hn[2][NS * SH];     // sample-major: H1..H4, then dZ4..dZ2
+    __attribute__((aligned(16))) __bf16 tr[NT][32 * SP];    // a wave's tile, unit-major, on its way out
+    __attribute__((aligned(16))) __bf16 h0n[NS * SI];
+    __attribute__((aligned(16))) __bf16 h0t[NF * ST];
+    __attribute__((aligned(16))) __bf16 dyn[NS * SI];
+    __attribute__((aligned(16))) __bf16 dyt[NO * ST];       // rows 9..15 zero
+    __attribute__((aligned(16))) float bias[BROW];
+    float yf[NS * 17];                                      // Y, then dY in columns 0..8
+    float xm[NF], xs[NF], ym[NO], ys[NO];
+    double ll[512];
+};
+
+// Forward, loss (mean over samples of sum_o<9 (y_o - t_o)^2 on standardised targets) and
+// backward of B samples, tile by tile; wave rt computes units 32 rt .. of every layer for the
+// tile's 32 CT samples.  sf: fragments of every 16-sample group, [fragment][group][512].
+// The weights (800 KB of fragments, two directions) stream from L2 once per tile.  Bound by the
+// chain of twelve dependent phases of 1.2 to 2 us (products, activations, LDS both ways):
+// 20 us for one tile per workgroup.  An Adam step at batch 4096 takes 35.9 us (this kernel
+// 20, the weight gradients 7, the reduction 5, the packing 3); a kernel per layer with
+// activations in memory, per-lane weight conversions and one thread per bias took 2113 us.
+template <int CT>
+__global__ __launch_bounds__(512) void lite_train_kernel(int64_t B, const float* __restrict__ p,
+                                                         const __bf16* __restrict__ img,
+                                                         const float* __restrict__ feats,
+                                                         const float* __restrict__ T, int64_t groups,
+                                                         __bf16* __restrict__ sf, float* __restrict__ bpart,
+                                                         double* __restrict__ lpart) {
+    using S = TrainShared<CT>;
+    constexpr int NS = S::NS, BLOCK = 512, ITEMS = (NS * 9 + BLOCK - 1) / BLOCK;
+    __shared__ S sm;
+    int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
+    const int rt = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: fragment bases in SGPRs
+    const double invB = 1.0 / (double)B;
+    for (int t = tid; t < NO * S::ST; t += BLOCK) sm.dyt[t] = (__bf16)0.0f;
+    for (int t = tid; t < NS * S::SI; t += BLOCK) sm.dyn[t] = (__bf16)0.0f;
+    for (int t = tid; t < 4 * NH; t += BLOCK)
+        sm.bias[t] = p[OFF_B1 + (t / NH) * (OFF_B2 - OFF_B1) + t % NH];   // b1 .. b4, equally spaced
+    if (tid < 16) {
+        sm.bias[4 * NH + tid] = p[OFF_B5 + tid];
+        sm.xm[tid] = p[OFF_XM + tid];
+        sm.xs[tid] = p[OFF_XS + tid];
+        sm.ym[tid] = p[OFF_YM + tid];
+        sm.ys[tid] = p[OFF_YS + tid];
+    }
+    // the inputs of a tile: thread -> sample tid / 16 (and 32 further), feature tid % 16
+    // (samples from B on read the last one's; their output gradients are zero)
+    float fx[CT];
+    auto load_inputs = [&](int64_t n0) {
 #pragma unroll
-        for (int s = 0; s < KSN; ++s) {
-            bf16x8 a;
+        for (int u = 0; u < CT; ++u) fx[u] = feats[min(n0 + (tid >> 4) + 32 * u, B - 1) * NF + (tid & 15)];
+    };
+    float bs[4] = {0.0f, 0.0f, 0.0f, 0.0f}, b5 = 0.0f;   // bias gradients, units as row_sums() leaves them
+    double loss = 0.0;
+    load_inputs((int64_t)blockIdx.x * NS);
+    lds_barrier();
+
+    const int64_t tiles = (B + NS - 1) / NS;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t n0 = tile * NS, g0 = tile * 2 * CT;
+        // nothing that a tile reads or addresses is kept in registers over the loop
+        __asm__ volatile("" ::: "memory");
+        __asm__ volatile("" : "+v"(tid), "+v"(lane), "+v"(h), "+v"(c));
+        // the wave's tile of fragment f, samples 32 ct ..: v to LDS (for the next layer) and out
+        auto put_out = [&](auto inner, const float (&v)[16], __bf16* hs, int ct, int f) {
+            put_tile<decltype(inner)::value>(hs, S::SH, sm.tr[rt] - rt * 32 * S::SP - ct * 32, S::SP, ct * 32 + c, rt * 32, h,
+                                             v);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = (__bf16)(m < M ? W[m * K + 16 * s + 8 * h + i] : 0.0f);
-            acc = mfma32(a, bfr[s], acc);
-        }
-        if (valid) {
+            for (int s = 0; s < 2; ++s)
+                *(bf16x8*)(sf + (((int64_t)(f + rt) * groups + g0 + 2 * ct + s) * 64 + lane) * 8) =
+                    *(const bf16x8*)(sm.tr[rt] + c * S::SP + 16 * s + 8 * h);
+        };
+        // products of the wave's units with the tile's samples; M fragments from nf on (a later
+        // layer's weights) are loaded into nw in between, one per k-step: issued together, 128
+        // KB over the workgroup at 64 B per cycle, they hold the waves up for as long as the
+        // products take (0.7 of a 2.0 us layer)
+        auto products = [&](auto ks, const bf16x8* a, const __bf16* hin, int stride, f32x16 (&acc)[CT], auto more, int nf,
+                            bf16x8* nw) {
+            constexpr int K = decltype(ks)::value, M = decltype(more)::value;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int mm = mt * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-                if (mm < M) {
-                    const float z = acc[j] + bias[mm];
-                    Z[n * M + mm] = z;
-                    if (ACT) Hout[n * M + mm] = (__bf16)fmaxf(z, 0.0f);
+            for (int t = 0; t < CT; ++t) acc[t] = f32x16{};
+            bf16x8 b[2][CT];
+            auto read = [&](int s) {
+#pragma unroll
+                for (int t = 0; t < CT; ++t) b[s & 1][t] = *(const bf16x8*)(hin + (t * 32 + c) * stride + 16 * s + 8 * h);
+            };
+            read(0);
+#pragma unroll
+            for (int s = 0; s < (K > M ? K : M); ++s) {
+                if (s + 1 < K) read(s + 1);
+                if (s < K)
+#pragma unroll
+                    for (int t = 0; t < CT; ++t) acc[t] = mfma32(a[s], b[s & 1][t], acc[t]);
+                if (s < M) nw[s] = *(const bf16x8*)(img + ((nf + s) * 64 + lane) * 8);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        using K0 = std::integral_constant<int, 0>;
+        using K1 = std::integral_constant<int, 1>;
+        using KH = std::integral_constant<int, KS>;
+        uint32_t mask[4][CT];   // bit j: z > 0 in row j
+        auto activate = [&](const f32x16 (&acc)[CT], int l, __bf16* hs) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+                float a[16];
+                uint32_t m = 0;
+#pragma unroll
+                for (int jq = 0; jq < 4; ++jq) {
+                    const float4 b = *(const float4*)(sm.bias + l * NH + rt * 32 + 8 * jq + 4 * h);
+                    const float bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float z = acc[t][4 * jq + e] + bb[e];
+                        a[4 * jq + e] = fmaxf(z, 0.0f);
+                        m |= z > 0.0f ? 1u << (4 * jq + e) : 0u;
+                    }
                 }
+                __asm__ volatile("" : "+v"(m));   // the bits, not the 16 values behind them
+                mask[l][t] = m;
+                put_out(std::true_type{}, a, hs, t, SF_H + l * NT);
+            }
+        };
+        auto backward = [&](auto inner, const f32x16 (&acc)[CT], int l, __bf16* zs) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+                float dz[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) dz[j] = (mask[l][t] >> j) & 1u ? acc[t][j] : 0.0f;
+                bs[l] += row_sums(dz, lane);
+                put_out(inner, dz, zs, t, SF_Z + l * NT);
+            }
+        };
+        bf16x8 w1[1], wa[KS], wb[KS];
+        load_frags<1>(img, FR_F1 + rt, lane, w1);
+        load_frags<KS>(img, FR_F2 + rt * KS, lane, wa);
+#pragma unroll
+        for (int u = 0; u < CT; ++u) {
+            const int n = (tid >> 4) + 32 * u, k = tid & 15;
+            const __bf16 q = (__bf16)((fx[u] - sm.xm[k]) / sm.xs[k]);
+            sm.h0n[n * S::SI + k] = q;
+            sm.h0t[k * S::ST + n] = q;
+        }
+        // item it of the loss: sample it / 9 of the tile, output it % 9
+        float tv[ITEMS];
+#pragma unroll
+        for (int u = 0; u < ITEMS; ++u) {
+            const int it = min(tid + u * BLOCK, NS * 9 - 1), i = it / 9;
+            tv[u] = T[min(n0 + i, B - 1) * NO + (it - 9 * i)];
+        }
+        lds_barrier();
+        f32x16 acc[CT];
+        products(K1{}, w1, sm.h0n, S::SI, acc, KH{}, FR_F2 + (NT + rt) * KS, wb);
+        activate(acc, 0, sm.hn[0]);
+        if (rt < 2 * CT)
+            *(bf16x8*)(sf + (((int64_t)SF_H0 * groups + g0 + rt) * 64 + lane) * 8) =
+                *(const bf16x8*)(sm.h0t + (c & 15) * S::ST + 16 * rt + 8 * h);
+        lds_barrier();
+        products(KH{}, wa, sm.hn[0], S::SH, acc, KH{}, FR_F2 + (2 * NT + rt) * KS, wa);
+        activate(acc, 1, sm.hn[1]);
+        lds_barrier();
+        products(KH{}, wb, sm.hn[1], S::SH, acc, K0{}, 0, wb);
+        if (rt < CT) load_frags<KS>(img, FR_F5, lane, wb);
+        activate(acc, 2, sm.hn[0]);
+        lds_barrier();
+        load_frags<1>(img, FR_T5 + rt, lane, w1);
+        products(KH{}, wa, sm.hn[0], S::SH, acc, KH{}, FR_T2 + (2 * NT + rt) * KS, wa);
+        activate(acc, 3, sm.hn[1]);
+        lds_barrier();
+        if (rt < CT) {
+            f32x16 y = f32x16{};
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                y = mfma32(wb[s], *(const bf16x8*)(sm.hn[1] + (rt * 32 + c) * S::SH + 16 * s + 8 * h), y);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int o = 8 * (j >> 2) + 4 * h + (j & 3);
+                sm.yf[(rt * 32 + c) * 17 + o] = y[j] + sm.bias[4 * NH + o];
             }
         }
-    }
-}
-
-// MSE of standardised targets: mean over samples of sum_o<9 (y_o - t_o)^2, dL/dY
-constexpr int LOSS_BLOCK = 256;
-__global__ __launch_bounds__(LOSS_BLOCK) void lite_loss_kernel(int64_t B, const float* __restrict__ p,
-                                                                const float* __restrict__ Y,
-                                                                const float* __restrict__ T,
-                                                                float* __restrict__ dY,
-                                                                double* __restrict__ lpart) {
-    __shared__ double sh[LOSS_BLOCK];
-    const int64_t n = (int64_t)blockIdx.x * LOSS_BLOCK + threadIdx.x;
-    double l = 0.0;
-    if (n < B) {
-        const double invB = 1.0 / (double)B;
+        load_frags<KS>(img, FR_T2 + (NT + rt) * KS, lane, wb);
+        lds_barrier();
 #pragma unroll
-        for (int o = 0; o < NO; ++o) {
+        for (int u = 0; u < ITEMS; ++u) {
+            const int it = tid + u * BLOCK, i = it / 9, o = it - 9 * i;
+            if (it >= NS * 9) continue;
             float d = 0.0f;
-            if (o < 9) {
-                const double t = ((double)T[n * NO + o] - p[OFF_YM + o]) / p[OFF_YS + o];
-                const double e = (double)Y[n * NO + o] - t;
-                l += e * e;
+            if (n0 + i < B) {
+                const double t = ((double)tv[u] - sm.ym[o]) / sm.ys[o];
+                const double e = (double)sm.yf[i * 17 + o] - t;
+                loss += e * e;
                 d = (float)(2.0 * e * invB);
             }
-            dY[n * NO + o] = d;
+            sm.yf[i * 17 + o] = d;
+            sm.dyn[i * S::SI + o] = (__bf16)d;
+            sm.dyt[o * S::ST + i] = (__bf16)d;
         }
+        lds_barrier();
+        products(K1{}, w1, sm.dyn, S::SI, acc, K0{}, 0, w1);
+        backward(std::true_type{}, acc, 3, sm.hn[0]);
+        if (rt < 2 * CT)
+            *(bf16x8*)(sf + (((int64_t)SF_DY * groups + g0 + rt) * 64 + lane) * 8) =
+                *(const bf16x8*)(sm.dyt + (c & 15) * S::ST + 16 * rt + 8 * h);
+        if (rt == 7) {
+            // the output bias: lane = output + 16 x quarter of the tile's samples
+#pragma unroll
+            for (int i = 0; i < NS / 4; ++i) b5 += sm.yf[((lane >> 4) * (NS / 4) + i) * 17 + (lane & 15)];
+        }
+        load_inputs((tile + gridDim.x) * NS);
+        lds_barrier();
+        products(KH{}, wa, sm.hn[0], S::SH, acc, KH{}, FR_T2 + rt * KS, wa);
+        backward(std::true_type{}, acc, 2, sm.hn[1]);
+        lds_barrier();
+        products(KH{}, wb, sm.hn[1], S::SH, acc, K0{}, 0, wb);
+        backward(std::true_type{}, acc, 1, sm.hn[0]);
+        lds_barrier();
+        products(KH{}, wa, sm.hn[0], S::SH, acc, K0{}, 0, wa);
+        backward(std::false_type{}, acc, 0, sm.hn[1]);
     }
-    sh[threadIdx.x] = l;
-    __syncthreads();
-    for (int s = LOSS_BLOCK / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+
+    float* out = bpart + (int64_t)blockIdx.x * BROW;
+    if (!(lane & 16)) {
+        const int j = lane & 15;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) out[l * NH + rt * 32 + 8 * (j >> 2) + 4 * h + (j & 3)] = bs[l];
     }
-    if (threadIdx.x == 0) lpart[blockIdx.x] = sh[0];
+    b5 += __shfl_xor(b5, 16, 64);
+    b5 += __shfl_xor(b5, 32, 64);
+    if (rt == 7 && lane < NO) out[4 * NH + lane] = lane < 9 ? b5 : 0.0f;
+    sm.ll[tid] = loss;
+    lds_barrier();
+    for (int s = BLOCK / 2; s > 0; s >>= 1) {
+        if (tid < s) sm.ll[tid] += sm.ll[tid + s];
+        lds_barrier();
+    }
+    if (tid == 0) lpart[blockIdx.x] = sm.ll[0];
 }
 
-__global__ void lite_loss_final_kernel(int nb, int64_t B, const double* __restrict__ lpart,
-                                       float* __restrict__ loss) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < nb; ++i) s += lpart[i];
-        *loss = (float)(s / (double)B);
-    }
-}
-
-// dH[n][k] = sum_m bf16(dZ[n][m]) bf16(W[m][k]);  dZprev[n][k] = dH * relu'(Zprev[n][k])
-template <int M, int K>
-__global__ __launch_bounds__(64) void lite_bwd_kernel(int64_t B, const float* __restrict__ W,
-                                                      const float* __restrict__ dZ,
-                                                      const float* __restrict__ Zprev,
-                                                      float* __restrict__ dZprev) {
-    constexpr int KT = K / 32, MS = M / 16;
-    const int lane = threadIdx.x, h = lane >> 5, c = lane & 31;
-    const int64_t n = (int64_t)blockIdx.x * 32 + c;
-    const bool valid = n < B;
-    bf16x8 bfr[MS];
+// weight gradients dZ^T H of one split of the sample groups: a wave takes 2 x 2 tiles of a
+// hidden layer (or four tiles of the first or the last), both operands straight from the
+// fragments (1 KB a load), four waves of a workgroup the four 64 x 64 quarters of 128 x 128
+constexpr int JOBS = 3 * 16 + 4, WG_BLOCK = 256;
+__global__ __launch_bounds__(WG_BLOCK) __attribute__((amdgpu_waves_per_eu(2, 2))) void lite_wgrad_kernel(int64_t groups, int splits, const __bf16* __restrict__ sf,
+                                                              float* __restrict__ part) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // the workgroups of one split share its fragments: on one XCD
+    const int lb = xcd_block(blockIdx.x, JOBS / 4 * splits), split = lb / (JOBS / 4);
+    const int job = (lb % (JOBS / 4)) * 4 + wave;
+    const int64_t g0 = groups * split / splits, g1 = groups * (split + 1) / splits;
+    float* out = part + (int64_t)split * GT_N * 1024;
+    auto run = [&](auto na, auto nb, int fa, int fb, int t0, int dt) {
+        constexpr int NA = decltype(na)::value, NB = decltype(nb)::value;
+        f32x16 acc[NA][NB];
 #pragma unroll
-    for (int s = 0; s < MS; ++s)
+        for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) bfr[s][i] = (__bf16)(valid ? dZ[n * M + 16 * s + 8 * h + i] : 0.0f);
-    for (int kt = 0; kt < KT; ++kt) {
-        const int k = kt * 32 + c;
-        f32x16 acc = f32x16{};
+            for (int k = 0; k < NB; ++k) acc[i][k] = f32x16{};
+        const __bf16* a0 = sf + ((int64_t)fa * groups * 64 + lane) * 8;
+        const __bf16* b0 = sf + ((int64_t)fb * groups * 64 + lane) * 8;
+        // rounds of U groups, the next round's fragments in flight during this one's products
+        // (left to itself the compiler waits for each load in turn: 14 against 8.5 us at 4096)
+        constexpr int U = 4;
+        struct Round {
+            bf16x8 a[U][NA], b[U][NB];
+        } r0, r1;
+        auto load = [&](Round& r, int64_t g) {
 #pragma unroll
-        for (int s = 0; s < MS; ++s) {
-            bf16x8 a;
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = min(g + u, g1 - 1);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = (__bf16)W[(16 * s + 8 * h + i) * K + k];
-            acc = mfma32(a, bfr[s], acc);
-        }
-        if (valid) {
+                for (int i = 0; i < NA; ++i) r.a[u][i] = *(const bf16x8*)(a0 + (i * groups + at) * 512);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int kk = kt * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-                dZprev[n * K + kk] = Zprev[n * K + kk] > 0.0f ? acc[j] : 0.0f;
+                for (int k = 0; k < NB; ++k) r.b[u][k] = *(const bf16x8*)(b0 + (k * groups + at) * 512);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto products = [&](const Round& r, int64_t g) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (g + u < g1)
+#pragma unroll
+                    for (int i = 0; i < NA; ++i)
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) acc[i][k] = mfma32(r.a[u][i], r.b[u][k], acc[i][k]);
+        };
+        load(r0, g0);
+        for (int64_t g = g0; g < g1; g += 2 * U) {
+            if (g + U < g1) load(r1, g + U);
+            products(r0, g);
+            if (g + 2 * U < g1) load(r0, g + 2 * U);
+            products(r1, g + U);
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+#pragma unroll
+                for (int jq = 0; jq < 4; ++jq)
+                    *(float4*)(out + (int64_t)(t0 + i * dt + k) * 1024 + jq * 256 + lane * 4) =
+                        make_float4(acc[i][k][4 * jq], acc[i][k][4 * jq + 1], acc[i][k][4 * jq + 2], acc[i][k][4 * jq + 3]);
+    };
+    using N1 = std::integral_constant<int, 1>;
+    using N2 = std::integral_constant<int, 2>;
+    using N4 = std::integral_constant<int, 4>;
+    if (job < 48) {
+        // layer l + 2 (W2 W3 W4): dZ of layer l + 2, H of layer l + 1
+        const int l = job / 16, q = (job % 16) / 4, w = job % 4;
+        const int mt = 4 * (q >> 1) + 2 * (w >> 1), kt = 4 * (q & 1) + 2 * (w & 1);
+        run(N2{}, N2{}, SF_Z + (l + 1) * NT + mt, SF_H + l * NT + kt, l * NT * NT + mt * NT + kt, NT);
+    } else if (job < 50) {
+        const int mt = 4 * (job - 48);
+        run(N4{}, N1{}, SF_Z + mt, SF_H0, GT_W1 + mt, 1);
+    } else {
+        const int kt = 4 * (job - 50);
+        run(N1{}, N4{}, SF_DY, SF_H + 3 * NT + kt, GT_W5 + kt, 0);
+    }
+}
+
+// grad = the splits' (weights) and the workgroups' (biases) partial sums added in order: ranges
+// of rows by the four waves, then the ranges, a float4 of four values per lane; with ADAM the
+// parameters are updated as well.  The last workgroup adds the loss.
+constexpr int RED_R = 4, RED_BLOCK = 64 * RED_R, RED_W = GT_N * 4, RED_B = (BROW / 4 + 63) / 64;
+template <bool ADAM>
+__global__ __launch_bounds__(RED_BLOCK) void lite_reduce_kernel(int splits, const float* __restrict__ part, int rows,
+                                                                const float* __restrict__ bpart,
+                                                                const double* __restrict__ lpart, int64_t B,
+                                                                float* __restrict__ grad, float* __restrict__ loss,
+                                                                AdamArgs ad) {
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    if (blockIdx.x == RED_W + RED_B) {
+        if (threadIdx.x >= 64) return;
+        double s = 0.0;
+        for (int i = lane; i < rows; i += 64) s += lpart[i];
+        s = group_sum<64>(s);
+        if (lane == 0) *loss = (float)(s / (double)B);
+        return;
+    }
+    __shared__ float4 red[RED_R][64];
+    // parameter of the lane's first value, the stride to the next ones, and whether they exist
+    const float* src;
+    int64_t q, row_len;
+    int st = 1, n;
+    bool live = true;
+    if (blockIdx.x < RED_W) {
+        const int t = blockIdx.x >> 2, row = 8 * (blockIdx.x & 3) + 4 * (lane >> 5), col = lane & 31;
+        src = part + ((int64_t)blockIdx.x * 64 + lane) * 4;
+        row_len = GT_N * 1024;
+        n = splits;
+        st = NH;
+        if (t < GT_W1)
+            q = OFF_W2 + (t / (NT * NT)) * (OFF_W3 - OFF_W2) + ((t / NT % NT) * 32 + row) * NH + (t % NT) * 32 + col;
+        else if (t < GT_W5) {
+            st = NF;
+            q = OFF_W1 + ((t - GT_W1) * 32 + row) * NF + col;
+            live = col < NF;
+        } else {
+            q = OFF_W5 + row * NH + (t - GT_W5) * 32 + col;
+            live = row < NO;
+        }
+    } else {
+        const int i = ((blockIdx.x - RED_W) * 64 + lane) * 4;
+        src = bpart + i;
+        row_len = BROW;
+        n = rows;
+        live = i < BROW;
+        const int l = min(i / NH, 4);
+        q = (l == 0 ? OFF_B1 : l == 1 ? OFF_B2 : l == 2 ? OFF_B3 : l == 3 ? OFF_B4 : OFF_B5) + i - l * NH;
+    }
+    float pq[4], mq[4], vq[4];
+    if (ADAM && r == 0 && live) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            pq[e] = ad.p[q + e * st];
+            mq[e] = ad.m[q + e * st];
+            vq[e] = ad.v[q + e * st];
         }
     }
-}
-
-// partial weight gradient of one chunk: part[chunk][woff + m K + k] = sum_n bf16(dZ[n][m]) H[n][k]
-template <int M, int K>
-__global__ __launch_bounds__(64) void lite_wgrad_kernel(int64_t B, const float* __restrict__ dZ,
-                                                        const __bf16* __restrict__ H,
-                                                        float* __restrict__ part, int64_t pstride,
-                                                        int64_t woff) {
-    constexpr int KT = (K + 31) / 32;
-    const int lane = threadIdx.x, h = lane >> 5, c = lane & 31;
-    const int chunk = blockIdx.y;
-    const int mt = blockIdx.x / KT, kt = blockIdx.x % KT;
-    const int m = mt * 32 + c, k = kt * 32 + c;
-    const int64_t n0 = (int64_t)chunk * TRAIN_CHUNK;
-    f32x16 acc = f32x16{};
-    for (int s = 0; s < TRAIN_CHUNK / 16; ++s) {
-        bf16x8 a, b;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int64_t n = n0 + 16 * s + 8 * h + i;
-            const bool v = n < B;
-            a[i] = (__bf16)((v && m < M) ? dZ[n * M + m] : 0.0f);
-            b[i] = (v && k < K) ? H[n * K + k] : (__bf16)0.0f;
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (live) {
+        const int r1 = (r + 1) * n / RED_R;
+#pragma unroll 8
+        for (int i = r * n / RED_R; i < r1; ++i) {
+            const float4 v = *(const float4*)(src + i * row_len);
+            s.x += v.x;
+            s.y += v.y;
+            s.z += v.z;
+            s.w += v.w;
         }
-        acc = mfma32(a, b, acc);
     }
-    if (k >= K) return;
-    float* dst = part + (int64_t)chunk * pstride + woff;
+    red[r][lane] = s;
+    __syncthreads();
+    if (r != 0 || !live) return;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int mm = mt * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-        if (mm < M) dst[mm * K + k] = acc[j];
+    for (int i = 1; i < RED_R; ++i) {
+        const float4 v = red[i][lane];
+        s.x += v.x;
+        s.y += v.y;
+        s.z += v.z;
+        s.w += v.w;
+    }
+    const float g[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        grad[q + e * st] = g[e];
+        if (ADAM) adam_one(ad, q + e * st, g[e], mq[e], vq[e], pq[e]);
     }
 }
 
-// partial bias gradient of one chunk: sum_n dZ[n][m] (sequential, FP32)
-__global__ void lite_bgrad_kernel(int64_t B, int M, const float* __restrict__ dZ,
-                                  float* __restrict__ part, int64_t pstride, int64_t boff) {
-    const int m = threadIdx.x;
-    const int chunk = blockIdx.x;
-    if (m >= M) return;
-    const int64_t n0 = (int64_t)chunk * TRAIN_CHUNK;
-    const int64_t n1 = n0 + TRAIN_CHUNK < B ? n0 + TRAIN_CHUNK : B;
-    float s = 0.0f;
-    for (int64_t n = n0; n < n1; ++n) s += dZ[n * M + m];
-    part[(int64_t)chunk * pstride + boff + m] = s;
-}
-
-// grad[q] = sum over chunks in order of part[chunk][q]
-__global__ void lite_reduce_kernel(int nchunk, const float* __restrict__ part, int64_t pstride,
-                                   float* __restrict__ grad) {
+__global__ void lite_adam_kernel(AdamArgs a, const float* __restrict__ g) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N_TRAIN) return;
-    float s = 0.0f;
-    for (int c = 0; c < nchunk; ++c) s += part[(int64_t)c * pstride + q];
-    grad[q] = s;
-}
-
-__global__ void lite_adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                                 float* __restrict__ v, float lr, float b1, float b2, float eps, float c1,
-                                 float c2) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N_TRAIN) return;
-    const float gq = g[q];
-    const float mq = b1 * m[q] + (1.0f - b1) * gq;
-    const float vq = b2 * v[q] + (1.0f - b2) * gq * gq;
-    m[q] = mq;
-    v[q] = vq;
-    p[q] -= lr * (mq / c1) / (sqrtf(vq / c2) + eps);
+    if (q < N_TRAIN) adam_one(a, q, g[q], a.m[q], a.v[q], a.p[q]);
 }
 
 // raw inputs of a batch of moment records (nvol per record, or the configuration's)
@@ -497,9 +759,9 @@ struct fp_lite {
     __bf16* img = nullptr;
     float* sec = nullptr;
     float* ybuf = nullptr;   // [ncell][16] normalised coefficients of the last closure
-    __bf16 *H0 = nullptr, *H[4] = {};
-    float *Z[4] = {}, *Y = nullptr, *dY = nullptr, *dZa = nullptr, *dZb = nullptr;
-    float *part = nullptr, *grad = nullptr;
+    // training scratch: weight fragments, sample fragments, partial gradients and losses
+    __bf16 *timg = nullptr, *sf = nullptr;
+    float *part = nullptr, *bpart = nullptr, *grad = nullptr;
     double* lpart = nullptr;
 };
 
@@ -511,12 +773,16 @@ static bool lalloc(T** p, size_t count) {
 extern "C" void fp_lite_destroy(fp_lite* n) {
     if (!n) return;
     (void)hipDeviceSynchronize();
-    for (void* q : {(void*)n->img, (void*)n->sec, (void*)n->ybuf, (void*)n->H0, (void*)n->H[0], (void*)n->H[1],
-                    (void*)n->H[2], (void*)n->H[3], (void*)n->Z[0], (void*)n->Z[1], (void*)n->Z[2],
-                    (void*)n->Z[3], (void*)n->Y, (void*)n->dY, (void*)n->dZa, (void*)n->dZb, (void*)n->part,
-                    (void*)n->grad, (void*)n->lpart})
+    for (void* q : {(void*)n->img, (void*)n->sec, (void*)n->ybuf, (void*)n->timg, (void*)n->sf, (void*)n->part,
+                    (void*)n->bpart, (void*)n->grad, (void*)n->lpart})
         (void)hipFree(q);
     delete n;
+}
+
+// 16-sample groups of a batch (whole 64-sample tiles) and the splits of its weight gradients
+static int64_t groups_of(int64_t B) { return (B + 63) / 64 * 4; }
+static int splits_of(int64_t B) {
+    return (int)std::min<int64_t>(MAX_SPLITS, (groups_of(B) + SPLIT_GROUPS - 1) / SPLIT_GROUPS);
 }
 
 extern "C" int fp_lite_create(fp_ctx* c, int64_t max_batch, fp_lite** out) {
@@ -526,14 +792,13 @@ extern "C" int fp_lite_create(fp_ctx* c, int64_t max_batch, fp_lite** out) {
     if (!n) return FP_ENOMEM;
     n->ctx = c;
     n->max_batch = max_batch;
-    const size_t B = (size_t)max_batch;
-    const size_t nchunk = (B + TRAIN_CHUNK - 1) / TRAIN_CHUNK;
     bool ok = lalloc(&n->img, IMG_BF) && lalloc(&n->sec, SEC_N) && lalloc(&n->ybuf, (size_t)c->ncell * NO);
-    if (ok && B > 0) {
-        ok = lalloc(&n->H0, B * NF) && lalloc(&n->Y, B * NO) && lalloc(&n->dY, B * NO) &&
-             lalloc(&n->dZa, B * NH) && lalloc(&n->dZb, B * NH) && lalloc(&n->part, nchunk * N_TRAIN) &&
-             lalloc(&n->grad, N_PARAMS) && lalloc(&n->lpart, B / LOSS_BLOCK + 1);
-        for (int l = 0; l < 4 && ok; ++l) ok = lalloc(&n->H[l], B * NH) && lalloc(&n->Z[l], B * NH);
+    if (ok && max_batch > 0) {
+        // enough for every batch up to max_batch
+        const size_t rows = (size_t)std::min<int64_t>(TRAIN_MAX_WG, (max_batch + 31) / 32);
+        ok = lalloc(&n->timg, FR_N * 512) && lalloc(&n->sf, (size_t)SF_N * groups_of(max_batch) * 512) &&
+             lalloc(&n->part, (size_t)splits_of(max_batch) * GT_N * 1024) && lalloc(&n->bpart, rows * BROW) &&
+             lalloc(&n->grad, N_PARAMS) && lalloc(&n->lpart, rows);
     }
     if (!ok) {
         fp_lite_destroy(n);
@@ -595,64 +860,48 @@ extern "C" int fp_lite_targets(fp_ctx* c, const double* rec, int64_t n, float* t
     return check_launch(c, "fp_lite_targets");
 }
 
+// gradient (and, with ad, the Adam step on it); the arguments are checked
+static int train_launch(fp_ctx* c, fp_lite* n, const float* params, const float* feats, const float* targets,
+                        int64_t B, float* grad, float* loss, const AdamArgs* ad, const char* what, hipStream_t s) {
+    hipLaunchKernelGGL(lite_train_pack_kernel, dim3(FR_N), dim3(64), 0, s, params, n->timg);
+    // tiles of 32 samples while they fit on the CUs at once, else of 64 (each weight read
+    // serves twice the samples), a workgroup per CU: 47 us at 8192 samples, 53 us at 8193
+    const bool small = B <= 32 * TRAIN_MAX_WG;
+    const int rows = small ? (int)((B + 31) / 32) : (int)std::min<int64_t>(TRAIN_MAX_WG, (B + 63) / 64);
+    const int64_t groups = small ? (int64_t)rows * 2 : groups_of(B);
+    const int splits = splits_of(B);
+    hipLaunchKernelGGL(small ? lite_train_kernel<1> : lite_train_kernel<2>, dim3(rows), dim3(512), 0, s, B, params,
+                       (const __bf16*)n->timg, feats, targets, groups, n->sf, n->bpart, n->lpart);
+    hipLaunchKernelGGL(lite_wgrad_kernel, dim3(JOBS / 4 * splits), dim3(WG_BLOCK), 0, s, groups, splits,
+                       (const __bf16*)n->sf, n->part);
+    const dim3 rgrid(RED_W + RED_B + 1);
+    if (ad)
+        hipLaunchKernelGGL(lite_reduce_kernel<true>, rgrid, dim3(RED_BLOCK), 0, s, splits, (const float*)n->part, rows,
+                           (const float*)n->bpart, (const double*)n->lpart, B, grad, loss, *ad);
+    else
+        hipLaunchKernelGGL(lite_reduce_kernel<false>, rgrid, dim3(RED_BLOCK), 0, s, splits, (const float*)n->part, rows,
+                           (const float*)n->bpart, (const double*)n->lpart, B, grad, loss, AdamArgs{});
+    return check_launch(c, what);
+}
+
+static bool grad_args(const fp_ctx* c, const fp_lite* n, const float* params, const float* feats, const float* targets,
+                      int64_t B, const float* grad, const float* loss) {
+    return c && n && params && feats && targets && grad && loss && B > 0 && B <= n->max_batch && n->ctx == c;
+}
+
 extern "C" int fp_lite_grad(fp_ctx* c, fp_lite* n, const float* params, const float* feats,
                             const float* targets, int64_t B, float* grad, float* loss, hipStream_t s) {
-    if (!c || !n || !params || !feats || !targets || !grad || !loss || B <= 0 || B > n->max_batch ||
-        n->ctx != c)
+    if (!grad_args(c, n, params, feats, targets, B, grad, loss))
         return set_err(c, FP_EINVAL, "fp_lite_grad: bad argument");
-    const unsigned g32 = (unsigned)((B + 31) / 32);
-    const int nchunk = (int)((B + TRAIN_CHUNK - 1) / TRAIN_CHUNK);
-    const int64_t ps = N_TRAIN;
-    hipLaunchKernelGGL(lite_input_kernel, dim3((unsigned)((B * NF + 255) / 256)), dim3(256), 0, s, B, feats,
-                       params, n->H0);
-    hipLaunchKernelGGL((lite_fwd_kernel<NF, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W1,
-                       params + OFF_B1, n->H0, n->Z[0], n->H[0]);
-    hipLaunchKernelGGL((lite_fwd_kernel<NH, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W2,
-                       params + OFF_B2, n->H[0], n->Z[1], n->H[1]);
-    hipLaunchKernelGGL((lite_fwd_kernel<NH, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W3,
-                       params + OFF_B3, n->H[1], n->Z[2], n->H[2]);
-    hipLaunchKernelGGL((lite_fwd_kernel<NH, NH, true>), dim3(g32), dim3(64), 0, s, B, params + OFF_W4,
-                       params + OFF_B4, n->H[2], n->Z[3], n->H[3]);
-    hipLaunchKernelGGL((lite_fwd_kernel<NH, NO, false>), dim3(g32), dim3(64), 0, s, B, params + OFF_W5,
-                       params + OFF_B5, n->H[3], n->Y, (__bf16*)nullptr);
-    const int nb = (int)((B + LOSS_BLOCK - 1) / LOSS_BLOCK);
-    hipLaunchKernelGGL(lite_loss_kernel, dim3(nb), dim3(LOSS_BLOCK), 0, s, B, params, n->Y, targets, n->dY,
-                       n->lpart);
-    hipLaunchKernelGGL(lite_loss_final_kernel, dim3(1), dim3(64), 0, s, nb, B, n->lpart, loss);
-    // output layer: dZ5 = dY
-    hipLaunchKernelGGL((lite_wgrad_kernel<NO, NH>), dim3(NH / 32, nchunk), dim3(64), 0, s, B, n->dY, n->H[3],
-                       n->part, ps, OFF_W5);
-    hipLaunchKernelGGL(lite_bgrad_kernel, dim3(nchunk), dim3(256), 0, s, B, NO, n->dY, n->part, ps, OFF_B5);
-    hipLaunchKernelGGL((lite_bwd_kernel<NO, NH>), dim3(g32), dim3(64), 0, s, B, params + OFF_W5, n->dY, n->Z[3],
-                       n->dZa);
-    // hidden layers 4, 3, 2 (weights W4, W3, W2; inputs H[2], H[1], H[0])
-    const int64_t woff[3] = {OFF_W4, OFF_W3, OFF_W2}, boff[3] = {OFF_B4, OFF_B3, OFF_B2};
-    float* dz[2] = {n->dZa, n->dZb};
-    for (int q = 0; q < 3; ++q) {
-        const int l = 3 - q;   // index of this layer's input activation H[l - 1] / Z[l - 1]
-        hipLaunchKernelGGL((lite_wgrad_kernel<NH, NH>), dim3(NT * NT, nchunk), dim3(64), 0, s, B, dz[q & 1],
-                           n->H[l - 1], n->part, ps, woff[q]);
-        hipLaunchKernelGGL(lite_bgrad_kernel, dim3(nchunk), dim3(256), 0, s, B, NH, dz[q & 1], n->part, ps,
-                           boff[q]);
-        hipLaunchKernelGGL((lite_bwd_kernel<NH, NH>), dim3(g32), dim3(64), 0, s, B, params + woff[q], dz[q & 1],
-                           n->Z[l - 1], dz[(q + 1) & 1]);
-    }
-    // layer 1 (input H0)
-    hipLaunchKernelGGL((lite_wgrad_kernel<NH, NF>), dim3(NT, nchunk), dim3(64), 0, s, B, dz[1], n->H0, n->part,
-                       ps, OFF_W1);
-    hipLaunchKernelGGL(lite_bgrad_kernel, dim3(nchunk), dim3(256), 0, s, B, NH, dz[1], n->part, ps, OFF_B1);
-    hipLaunchKernelGGL(lite_reduce_kernel, dim3((unsigned)((N_TRAIN + 255) / 256)), dim3(256), 0, s, nchunk,
-                       n->part, ps, grad);
-    return check_launch(c, "fp_lite_grad");
+    return train_launch(c, n, params, feats, targets, B, grad, loss, nullptr, "fp_lite_grad", s);
 }
 
 extern "C" int fp_lite_adam(fp_ctx* c, float* params, const float* grad, float* m, float* v, int64_t t,
                             float lr, hipStream_t s) {
     if (!c || !params || !grad || !m || !v || t < 1 || !(lr >= 0.0f))
         return set_err(c, FP_EINVAL, "fp_lite_adam: bad argument");
-    const float c1 = (float)(1.0 - pow(0.9, (double)t)), c2 = (float)(1.0 - pow(0.999, (double)t));
-    hipLaunchKernelGGL(lite_adam_kernel, dim3((unsigned)((N_TRAIN + 255) / 256)), dim3(256), 0, s, params, grad,
-                       m, v, lr, 0.9f, 0.999f, 1e-8f, c1, c2);
+    hipLaunchKernelGGL(lite_adam_kernel, dim3((unsigned)((N_TRAIN + 255) / 256)), dim3(256), 0, s,
+                       adam_args(params, m, v, t, lr), grad);
     return check_launch(c, "fp_lite_adam");
 }
 
@@ -660,9 +909,15 @@ extern "C" int fp_lite_train_step(fp_ctx* c, fp_lite* n, float* params, float* m
                                   float lr, const float* feats, const float* targets, int64_t B, float* loss,
                                   hipStream_t s) {
     if (!n) return set_err(c, FP_EINVAL, "fp_lite_train_step: bad argument");
-    const int rc = fp_lite_grad(c, n, params, feats, targets, B, n->grad, loss, s);
-    if (rc) return rc;
-    return fp_lite_adam(c, params, n->grad, m, v, t, lr, s);
+    if (!grad_args(c, n, params, feats, targets, B, n->grad, loss))
+        return set_err(c, FP_EINVAL, "fp_lite_grad: bad argument");
+    if (!m || !v || t < 1 || !(lr >= 0.0f)) {
+        // as the two calls would: the gradient and the loss, then the refusal
+        const int rc = train_launch(c, n, params, feats, targets, B, n->grad, loss, nullptr, "fp_lite_grad", s);
+        return rc ? rc : set_err(c, FP_EINVAL, "fp_lite_adam: bad argument");
+    }
+    const AdamArgs ad = adam_args(params, m, v, t, lr);
+    return train_launch(c, n, params, feats, targets, B, n->grad, loss, &ad, "fp_lite_train_step", s);
 }
 
 // ---- column statistics of a training matrix (the standardising scaler of Sec. "Phase 3":

@@ -14,6 +14,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import lite_oracle as L
 from oracle import mlp_oracle as M
 from paper_2606_15622_amd import inputs as I
 
@@ -108,3 +109,29 @@ def test_network_gradient(B, loss_kind):
     full = loss.clone()
     check_sum(B, M.SHAPES[:8], total, grad_of)
     check_step(net, ctx.nn_adam, pd, args(0, B), total, full)
+
+
+@pytest.mark.parametrize("B", SIZES)
+def test_lite_gradient(B):
+    F = fp()
+    rng = np.random.default_rng(B)
+    feats = dev(2.0 * rng.standard_normal((B, 16)))
+    t = np.zeros((B, 16))
+    t[:, :9] = rng.integers(1, 8, (B, 9)) * FAR
+    ctx = F.Context(I.couette(ncell=1), 1)
+    net = F.LiteNetwork(ctx, B)
+    pd = dev(flat_params(L.SHAPES, 9, B))
+    loss = torch.zeros(1, device="cuda")
+
+    def args(i0, i1):
+        return feats[i0:i1].contiguous(), dev((i1 - i0) * t[i0:i1]), i1 - i0
+
+    def grad_of(i0, i1):
+        g = torch.zeros(F.LITE_PARAMS, device="cuda")
+        net.grad(pd, *args(i0, i1), g, loss)
+        return g
+
+    total = grad_of(0, B)
+    full = loss.clone()
+    check_sum(B, L.SHAPES[:10], total, grad_of)
+    check_step(net, ctx.lite_adam, pd, args(0, B), total, full)
