@@ -38,23 +38,10 @@ __global__ __launch_bounds__(CL_BLOCK) void closure_kernel(fp_config g, int32_t 
 #pragma unroll
     for (int i = 0; i < 31; ++i) finite = finite && isfinite(m[i]);
     const double N = m[M_N], theta = m[M_TH];
-    int st = FP_CELL_OK;
-    if (N <= 1.0)
-        st = FP_CELL_EMPTY;
-    else if (!finite)
-        st = FP_CELL_NONFINITE;
-    else if (!(theta > 0.0))
-        st = FP_CELL_EMPTY;
-    double out[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) out[i] = 0.0;
-    if (st != FP_CELL_OK) {
-        out[R_E] = 1.0;
-        out[R_TH] = finite ? theta : 0.0;
-    } else {
-        const double tau = cell_tau(g, N * (nvol ? nvol[cell] : g.fnum_over_vol), theta);
-        const double eps2 = g.eps_hat / (theta * tau);
-        double y[9];
+    int st = cell_class(N, theta, finite);
+    double tau = 0.0, y[9];
+    if (st == FP_CELL_OK) {
+        tau = cell_tau(g, N * (nvol ? nvol[cell] : g.fnum_over_vol), theta);
         if (N < (double)g.n_min) {
             st = FP_CELL_FEW;
         } else {
@@ -103,30 +90,9 @@ __global__ __launch_bounds__(CL_BLOCK) void closure_kernel(fp_config g, int32_t 
             }
             if (accepted) st = FP_CELL_NN;
         }
-        if (st == FP_CELL_OK || st == FP_CELL_NN || st == FP_CELL_NN_FALLBACK) {
-            const double it = 1.0 / tau;
-            const double ig = 1.0 / (tau * sqrt(theta));
-#pragma unroll
-            for (int i = 0; i < 6; ++i) out[R_C + i] = y[i] * it;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) out[R_G + i] = y[6 + i] * ig;
-            out[R_EPS2] = eps2;
-            if (NN && st == FP_CELL_NN && relax < 1.0) {
-                const double* prev = rec + (int64_t)cell * REC;
-                const int pst = (int)prev[R_ST];
-                if (pst == FP_CELL_OK || pst == FP_CELL_NN || pst == FP_CELL_NN_FALLBACK) {
-#pragma unroll
-                    for (int i = 0; i < 9; ++i)
-                        out[R_C + i] = relax * out[R_C + i] + (1.0 - relax) * prev[R_C + i];
-                }
-            }
-        }
-        out[R_TAU] = tau;
-        out[R_TH] = theta;
-        out[R_E] = exp(-g.dt / tau);
-        out[R_SIG] = sqrt(theta * (1.0 - exp(-2.0 * g.dt / tau)));
     }
-    out[R_ST] = (double)st;
+    double out[16];
+    update_record(g, st, theta, finite, tau, y, rec + (int64_t)cell * REC, relax, out);
     double* dst = rec + (int64_t)cell * REC;
 #pragma unroll
     for (int i = 0; i < 16; ++i) dst[i] = out[i];

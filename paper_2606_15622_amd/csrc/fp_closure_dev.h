@@ -128,4 +128,48 @@ __device__ __forceinline__ double cell_tau(const fp_config& g, double ndens, dou
     return 2.0 * mu / p;
 }
 
+// status of a cell before any solve: OK, or EMPTY / NONFINITE (left alone by the update)
+__device__ __forceinline__ int cell_class(double N, double theta, bool finite) {
+    if (N <= 1.0) return FP_CELL_EMPTY;
+    if (!finite) return FP_CELL_NONFINITE;
+    return theta > 0.0 ? FP_CELL_OK : FP_CELL_EMPTY;
+}
+
+// the update record of a cell of status st with normalised coefficients y (used for OK, NN
+// and NN_FALLBACK; the other solvable cells take the Langevin drift).  relax < 1 blends the
+// network's (NN) with those of the cell's previous record, when that carries any.
+__device__ __forceinline__ void update_record(const fp_config& g, int st, double theta, bool finite, double tau,
+                                              const double (&y)[9], const double* prev, double relax,
+                                              double (&out)[16]) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) out[i] = 0.0;
+    out[R_ST] = (double)st;
+    if (st == FP_CELL_EMPTY || st == FP_CELL_NONFINITE) {
+        out[R_E] = 1.0;
+        out[R_TH] = finite ? theta : 0.0;
+        return;
+    }
+    if (st == FP_CELL_OK || st == FP_CELL_NN || st == FP_CELL_NN_FALLBACK) {
+        const double it = 1.0 / tau;
+        const double ig = 1.0 / (tau * sqrt(theta));
+#pragma unroll
+        for (int i = 0; i < 6; ++i) out[R_C + i] = y[i] * it;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) out[R_G + i] = y[6 + i] * ig;
+        out[R_EPS2] = g.eps_hat / (theta * tau);
+        if (st == FP_CELL_NN && relax < 1.0) {
+            const int pst = (int)prev[R_ST];
+            if (pst == FP_CELL_OK || pst == FP_CELL_NN || pst == FP_CELL_NN_FALLBACK) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    out[R_C + i] = relax * out[R_C + i] + (1.0 - relax) * prev[R_C + i];
+            }
+        }
+    }
+    out[R_TAU] = tau;
+    out[R_TH] = theta;
+    out[R_E] = exp(-g.dt / tau);
+    out[R_SIG] = sqrt(theta * (1.0 - exp(-2.0 * g.dt / tau)));
+}
+
 }  // namespace fpg

@@ -40,7 +40,6 @@ constexpr int IMG_L1 = 0, IMG_L2 = 4096, IMG_L3 = 69632, IMG_L4 = 135168, IMG_L5
 // check kernel, which receives normalised coefficients
 constexpr int SEC_B1 = 0, SEC_B2 = 256, SEC_B3 = 512, SEC_B4 = 768, SEC_B5 = 1024, SEC_XM = 1040,
               SEC_XS = 1056, SEC_YM = 1072, SEC_YS = 1088, SEC_ID = 1104, SEC_N = 1136;
-constexpr int INF_BLOCK = 512;                  // 8 waves, 256 cells per workgroup
 constexpr int LDS_BF = NT * KS * 512;           // one hidden layer: 65536 BF16 (128 KB)
 
 static_assert(IMG_L2 - IMG_L1 == NT * 512 && IMG_L3 - IMG_L2 == LDS_BF && IMG_L5 - IMG_L4 == LDS_BF &&
@@ -120,138 +119,265 @@ __device__ __forceinline__ void cell_inputs(const fp_config& g, const double* __
 }
 
 // ---------------------------------------------------------------------------------------
-// fused inference.  mode 0: y[cell][16] = standardised network outputs (rows 9..15 zero);
-// mode 1: y[cell][16] = normalised coefficients [tau Ct - 5 eps_hat I (6), tau sqrt(theta)
-// Gamma (3), 0...] from the de-standardised outputs, for the check kernel with the
-// identity scaler.  Cells without inputs (N <= 1 or theta <= 0) are evaluated on zero
-// inputs in mode 0 and get zeros in mode 1.
-template <int MT_GROUP>
-__device__ __forceinline__ void hidden_layer(const __bf16* __restrict__ w, const float* __restrict__ bias,
-                                             const bf16x8 (&bin)[KS], bf16x8 (&bout)[KS], int lane) {
-    const int h = lane >> 5;
+// fused inference.  MODE 0: y[cell][16] = standardised network outputs (rows 9..15 zero);
+// MODE 1: y[cell][16] = normalised coefficients [tau Ct - 5 eps_hat I (6), tau sqrt(theta)
+// Gamma (3), 0...] from the de-standardised outputs, for the check kernel with the identity
+// scaler; MODE 2 (records through third order, unchecked): the update records themselves.
+// Cells without inputs (N <= 1 or theta <= 0) are evaluated on zero inputs in mode 0 and get
+// zeros in mode 1.
+//
+// A workgroup of W waves takes 32 cells per wave through the five layers in registers and goes
+// on to its next cells (a workgroup per CU).  The weights come in 26 chunks (layer 1, eight
+// 32-row tiles of each hidden layer, layer 5) through two LDS slots: chunk k + 1 is written and
+// chunk k + 3 loaded while chunk k multiplies, a barrier per chunk.  The next cells' moment
+// records trickle into LDS meanwhile, a 1 KB piece per chunk, and each tile's ReLU runs
+// between the next tile's MFMAs.  1e6 cells: 472 us in mode 2; a workgroup per 256 cells that
+// staged whole 128 KB layers between barriers and left the records to the check kernel took
+// 655 us.  Of a pass of 23 us at full clock the hidden layers take 16 (two thirds of their
+// MFMA rate), the FP64 inputs and records 5, the first layer 1.4.  Four waves of 64 cells
+// (half the LDS reads, twice the registers) were slower (490 to 600 us), and without any
+// fragment reads it would take 445: the LDS is not the bound.
+constexpr int CH_N = 26, CH_BF = KS * 512;   // chunks of a pass, bfloat16 of a chunk (layer 1: half)
+constexpr int MROW = MOM + 1;   // LDS row of a record: rows start on different banks
+
+template <int W>
+struct InferShared {
+    __attribute__((aligned(16))) __bf16 w[2][CH_BF];
+    double mom[W][32 * MROW];
+    __attribute__((aligned(16))) float sec[SEC_N];
+};
+
+template <int W>
+struct InferPass {
+    InferShared<W>& sm;
+    const __bf16* gimg;
+    const double* mom;
+    int32_t ncell, next;      // first cell of the wave's next pass
+    int tid, lane, wave, h, c;
+    static constexpr int BLOCK = 64 * W, SQ = 16 / W;   // 16-byte loads of a chunk per thread
+    bf16x8 st[2][SQ];         // chunks on their way to LDS
+    double2 piece;            // a piece of the next records on its way to LDS
+
+    // chunk k (mod CH_N) into the register set s
+    __device__ __forceinline__ void load(int k, int s) {
+        const int kk = k % CH_N;
+        const __bf16* src = gimg + (kk == 0 ? IMG_L1 : IMG_L2 + (kk - 1) * CH_BF);
 #pragma unroll
-    for (int mp = 0; mp < NT; mp += MT_GROUP) {
-        f32x16 acc[MT_GROUP];
+        for (int q = 0; q < SQ; ++q)
+            if (kk != 0 || 2 * q < SQ) st[s][q] = *(const bf16x8*)(src + (q * BLOCK + tid) * 8);
+    }
+    __device__ __forceinline__ void store(int k, int s) {
+        const int kk = k % CH_N;
 #pragma unroll
-        for (int t = 0; t < MT_GROUP; ++t)
+        for (int q = 0; q < SQ; ++q)
+            if (kk != 0 || 2 * q < SQ) *(bf16x8*)(sm.w[kk & 1] + (q * BLOCK + tid) * 8) = st[s][q];
+    }
+    // piece q of the next records (four of them, 16 bytes a lane), to registers and to LDS
+    __device__ __forceinline__ void load_piece(int q) {
+        const int64_t cell = min(next + 4 * q + (lane >> 4), ncell - 1);
+        const double* p = mom + cell * MOM + (lane & 15) * 2;
+        piece = make_double2(p[0], p[1]);
+    }
+    __device__ __forceinline__ void store_piece(int q) {
+        double* d = sm.mom[wave] + (4 * q + (lane >> 4)) * MROW + (lane & 15) * 2;
+        d[0] = piece.x;
+        d[1] = piece.y;
+    }
+    // the traffic behind chunk K, once it is in LDS for everyone (lds_barrier)
+    template <int K>
+    __device__ __forceinline__ void move() {
+        store(K + 1, (K + 1) & 1);
+        load(K + 3, (K + 1) & 1);
+        // pieces 0 .. 7 in chunks 2, 3, ...
+        if constexpr (K >= 3 && K - 3 < 8) store_piece(K - 3);
+        if constexpr (K >= 2 && K - 2 < 8) load_piece(K - 2);
+    }
+    // chunk K times bin into acc (16 k-steps); every fragment is read AHEAD k-steps before its
+    // products (one wave per SIMD: nothing else hides the LDS latency), between(s) runs
+    // between the products of step s and those of step s + 1
+    template <int K, typename F>
+    __device__ __forceinline__ void products(const bf16x8 (&bin)[KS], f32x16& acc, F between) {
+        constexpr int AHEAD = 4;
+        const __bf16* w = sm.w[K & 1] + lane * 8;
+        bf16x8 a[AHEAD];
 #pragma unroll
-            for (int jq = 0; jq < 4; ++jq) {
-                const float4 bq = *(const float4*)(bias + (mp + t) * 32 + 8 * jq + 4 * h);
-                acc[t][4 * jq + 0] = bq.x;
-                acc[t][4 * jq + 1] = bq.y;
-                acc[t][4 * jq + 2] = bq.z;
-                acc[t][4 * jq + 3] = bq.w;
-            }
+        for (int s = 0; s < AHEAD; ++s) a[s] = *(const bf16x8*)(w + s * 512);
+        move<K>();
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+        for (int s = 0; s < KS; ++s) {
+            acc = mfma32(a[s % AHEAD], bin[s], acc);
+            if (s + AHEAD < KS) a[s % AHEAD] = *(const bf16x8*)(w + (s + AHEAD) * 512);
+            between(s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ __forceinline__ f32x16 bias_of(const float* b, int mt) const {
+        f32x16 v;
 #pragma unroll
-            for (int t = 0; t < MT_GROUP; ++t) {
-                const bf16x8 a = *(const bf16x8*)(w + (((mp + t) * KS + s) * 64 + lane) * 8);
-                acc[t] = mfma32(a, bin[s], acc[t]);
-            }
+        for (int jq = 0; jq < 4; ++jq) {
+            const float4 q = *(const float4*)(b + mt * 32 + 8 * jq + 4 * h);
+            v[4 * jq + 0] = q.x;
+            v[4 * jq + 1] = q.y;
+            v[4 * jq + 2] = q.z;
+            v[4 * jq + 3] = q.w;
+        }
+        return v;
+    }
+};
+
+// rows 2 i, 2 i + 1 of the lane's tile mt through the ReLU
+__device__ __forceinline__ void relu_pair(const f32x16& acc, bf16x8 (&bout)[KS], int mt, int i) {
 #pragma unroll
-        for (int t = 0; t < MT_GROUP; ++t)
+    for (int j = 2 * i; j < 2 * i + 2; ++j) bout[2 * mt + (j >> 3)][j & 7] = (__bf16)fmaxf(acc[j], 0.0f);
+}
+
+// tiles MT .. of a hidden layer whose first tile is chunk K0; prev: the tile before this one
+template <int W, int K0, int MT>
+__device__ __forceinline__ void hidden_tiles(InferPass<W>& P, const float* bias, const bf16x8 (&bin)[KS],
+                                             bf16x8 (&bout)[KS], const f32x16& prev) {
+    if constexpr (MT < NT) {
+        f32x16 acc = P.bias_of(bias, MT);
+        lds_barrier();
+        P.template products<K0 + MT>(bin, acc, [&](int s) {
+            if (MT > 0 && (s & 1)) relu_pair(prev, bout, MT - 1, s >> 1);
+        });
+        hidden_tiles<W, K0, MT + 1>(P, bias, bin, bout, acc);
+    } else {
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                bout[2 * (mp + t) + (j >> 3)][j & 7] = (__bf16)fmaxf(acc[t][j], 0.0f);
+        for (int i = 0; i < 8; ++i) relu_pair(prev, bout, NT - 1, i);
     }
 }
 
-// copy n16 16-byte chunks of the image into LDS (all threads of the workgroup)
-__device__ __forceinline__ void stage(const __bf16* __restrict__ src, __bf16* __restrict__ dst, int n16) {
-    __syncthreads();
-    for (int t = threadIdx.x; t < n16; t += INF_BLOCK) ((bf16x8*)dst)[t] = ((const bf16x8*)src)[t];
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(INF_BLOCK) void lite_infer_kernel(fp_config g, int32_t ncell,
+template <int W, int MODE>
+__global__ __launch_bounds__(64 * W) void lite_infer_kernel(fp_config g, int32_t ncell,
                                                                const double* __restrict__ mom,
                                                                const double* __restrict__ nvol,
                                                                const __bf16* __restrict__ gimg,
                                                                const float* __restrict__ gsec,
-                                                               int mode, float* __restrict__ yout) {
-    __shared__ __attribute__((aligned(16))) __bf16 wl[LDS_BF];
-    __shared__ __attribute__((aligned(16))) float sec[SEC_N];
-    for (int t = threadIdx.x; t < SEC_N; t += INF_BLOCK) sec[t] = gsec[t];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
-    const int32_t cell = (blockIdx.x * (INF_BLOCK / 64) + wave) * 32 + n;
-    const bool valid = cell < ncell;
-    float f[NF];
+                                                               float* __restrict__ yout, double* __restrict__ rec,
+                                                               int32_t* __restrict__ status, double relax) {
+    __shared__ InferShared<W> sm;
+    constexpr int BLOCK = 64 * W, CELLS = 32;   // cells of a wave and pass
+    InferPass<W> P{sm, gimg, mom, ncell};
+    P.tid = threadIdx.x;
+    P.lane = threadIdx.x & 63;
+    P.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    P.h = P.lane >> 5;
+    P.c = P.lane & 31;
+    for (int t = threadIdx.x; t < SEC_N; t += BLOCK) sm.sec[t] = gsec[t];
+    P.next = (blockIdx.x * W + P.wave) * CELLS;
+    P.load(0, 0);
+    P.load(1, 1);
+    {
+        double2 all[8];
 #pragma unroll
-    for (int q = 0; q < NF; ++q) f[q] = 0.0f;
-    double tau = 1.0, th = 0.0;
-    bool feat = false;
-    if (valid) {
-        const double* mr = mom + (int64_t)cell * MOM;
-        th = mr[M_TH];
-        feat = mr[M_N] > 1.0 && th > 0.0;
-        if (feat) cell_inputs(g, mr, nvol ? nvol[cell] : g.fnum_over_vol, f, tau);
-    }
-    stage(gimg + IMG_L1, wl, (IMG_L2 - IMG_L1) / 8);   // also makes sec visible
-    bf16x8 b0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int K = 8 * h + i;
-        b0[i] = (__bf16)((f[K] - sec[SEC_XM + K]) / sec[SEC_XS + K]);
-    }
-    bf16x8 act0[KS], act1[KS];
-    // layer 1: K = 16, one k-step per output tile
-#pragma unroll
-    for (int mt = 0; mt < NT; ++mt) {
-        f32x16 acc;
-#pragma unroll
-        for (int jq = 0; jq < 4; ++jq) {
-            const float4 bq = *(const float4*)(sec + SEC_B1 + mt * 32 + 8 * jq + 4 * h);
-            acc[4 * jq + 0] = bq.x;
-            acc[4 * jq + 1] = bq.y;
-            acc[4 * jq + 2] = bq.z;
-            acc[4 * jq + 3] = bq.w;
+        for (int q = 0; q < 8; ++q) {
+            P.load_piece(q);
+            all[q] = P.piece;
         }
-        const bf16x8 a = *(const bf16x8*)(wl + (mt * 64 + lane) * 8);
-        acc = mfma32(a, b0, acc);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) act0[2 * mt + (j >> 3)][j & 7] = (__bf16)fmaxf(acc[j], 0.0f);
+        for (int q = 0; q < 8; ++q) {
+            P.piece = all[q];
+            P.store_piece(q);
+        }
     }
-    stage(gimg + IMG_L2, wl, LDS_BF / 8);
-    hidden_layer<2>(wl, sec + SEC_B2, act0, act1, lane);
-    stage(gimg + IMG_L3, wl, LDS_BF / 8);
-    hidden_layer<2>(wl, sec + SEC_B3, act1, act0, lane);
-    stage(gimg + IMG_L4, wl, LDS_BF / 8);
-    hidden_layer<2>(wl, sec + SEC_B4, act0, act1, lane);
-    stage(gimg + IMG_L5, wl, (IMG_BF - IMG_L5) / 8);
-    f32x16 acc = f32x16{};
+    P.store(0, 0);
+    P.load(2, 0);
+    // st[1] holds chunk 1, st[0] chunk 2: chunk k waits in set k & 1
+    for (int32_t first = blockIdx.x * W * CELLS; first < ncell; first += gridDim.x * W * CELLS) {
+        // no address is kept in registers over the loop (spilled, each would be reloaded behind
+        // the weights in flight)
+        __asm__ volatile("" : "+v"(P.tid), "+v"(P.lane), "+v"(P.h), "+v"(P.c)::"memory");
+        const int lane = P.lane, h = P.h, c = P.c;
+        // lane = cell (the upper half repeats the lower): its inputs
+        const int32_t cell = P.next + (lane & (CELLS - 1));
+        const bool valid = cell < ncell && lane < CELLS;
+        P.next += gridDim.x * W * CELLS;
+        double* mine = sm.mom[P.wave] + (lane & (CELLS - 1)) * MROW;
+        const double N = mine[M_N], th = mine[M_TH];
+        const bool feat = N > 1.0 && th > 0.0;
+        bool finite = true;
+        if constexpr (MODE == 2) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const bf16x8 a = *(const bf16x8*)(wl + (s * 64 + lane) * 8);
-        acc = mfma32(a, act1[s], acc);
-    }
-    // rows 0..3 and 8 live in half 0 (j = 0..3, 4), rows 4..7 in half 1 (j = 0..3)
-    float o[9];
+            for (int i = 0; i < 31; ++i) finite = finite && isfinite(mine[i]);
+        }
+        double tau = 1.0;
+        float f[NF];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float mine = acc[j];
-        o[j] = mine;
-        o[4 + j] = __shfl_xor(mine, 32, 64);
-    }
-    o[8] = acc[4];
-    if (valid && h == 0) {
-        float* dst = yout + (int64_t)cell * NO;
-        if (mode == 0) {
+        for (int q = 0; q < NF; ++q) f[q] = 0.0f;
+        if (feat) cell_inputs(g, mine, nvol && cell < ncell ? nvol[cell] : g.fnum_over_vol, f, tau);
+        // to LDS and back in the layout of the first product, in place of the records read
+        lds_barrier();
+        __bf16* xin = (__bf16*)sm.mom[P.wave];
+        bf16x8 x[2];
 #pragma unroll
-            for (int q = 0; q < 9; ++q) dst[q] = o[q] + sec[SEC_B5 + q];
-        } else {
+        for (int k = 0; k < NF; ++k) x[k >> 3][k & 7] = (__bf16)((f[k] - sm.sec[SEC_XM + k]) / sm.sec[SEC_XS + k]);
+        if (lane < CELLS) {
+            *(bf16x8*)(xin + lane * 24) = x[0];
+            *(bf16x8*)(xin + lane * 24 + 8) = x[1];
+        }
+        bf16x8 act0[KS], act1[KS];
+        lds_barrier();
+        P.template move<0>();
+        const bf16x8 b0 = *(const bf16x8*)(xin + c * 24 + 8 * h);
+#pragma unroll
+        for (int mt = 0; mt < NT; ++mt) {
+            const f32x16 acc =
+                mfma32(*(const bf16x8*)(sm.w[0] + (mt * 64 + lane) * 8), b0, P.bias_of(sm.sec + SEC_B1, mt));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) relu_pair(acc, act0, mt, i);
+        }
+        f32x16 acc = f32x16{};
+        hidden_tiles<W, 1, 0>(P, sm.sec + SEC_B2, act0, act1, acc);
+        hidden_tiles<W, 9, 0>(P, sm.sec + SEC_B3, act1, act0, acc);
+        hidden_tiles<W, 17, 0>(P, sm.sec + SEC_B4, act0, act1, acc);
+        lds_barrier();
+        P.template products<25>(act1, acc, [](int) {});
+        // lane = cell again: rows 0..3 and 8 live in half 0 (j = 0..3, 4), rows 4..7 in half 1
+        float o[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) o[q] = __shfl(acc[q < 8 ? q & 3 : 4], c + (q >= 4 && q < 8 ? 32 : 0), 64);
+        if (valid) {
+            float y[9];
             const double d6[6] = {1, 0, 0, 1, 0, 1};
             const double sth = feat ? sqrt(th) : 0.0;
 #pragma unroll
             for (int q = 0; q < 9; ++q) {
-                const double d = (double)(o[q] + sec[SEC_B5 + q]) * (double)sec[SEC_YS + q] +
-                                 (double)sec[SEC_YM + q];
-                double v = q < 6 ? tau * d - 5.0 * g.eps_hat * d6[q] : tau * sth * d;
-                dst[q] = feat ? (float)v : 0.0f;
+                y[q] = o[q] + sm.sec[SEC_B5 + q];
+                if constexpr (MODE != 0) {
+                    const double d = (double)y[q] * (double)sm.sec[SEC_YS + q] + (double)sm.sec[SEC_YM + q];
+                    const double v = q < 6 ? tau * d - 5.0 * g.eps_hat * d6[q] : tau * sth * d;
+                    y[q] = feat ? (float)v : 0.0f;
+                }
+            }
+            if constexpr (MODE == 2) {
+                double yd[9];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) yd[q] = (double)y[q];
+                yd[0] += 5.0 * g.eps_hat;
+                yd[3] += 5.0 * g.eps_hat;
+                yd[5] += 5.0 * g.eps_hat;
+                int st = cell_class(N, th, finite);
+                double out[16];
+                if (st == FP_CELL_OK) {
+                    if (N < (double)g.n_min) {
+                        st = FP_CELL_FEW;
+                    } else {
+                        st = FP_CELL_NN;
+#pragma unroll
+                        for (int q = 0; q < 9; ++q) st = isfinite(yd[q]) ? st : FP_CELL_SINGULAR;
+                    }
+                }
+                update_record(g, st, th, finite, tau, yd, rec + (int64_t)cell * REC, relax, out);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) rec[(int64_t)cell * REC + i] = out[i];
+                status[cell] = st;
+            } else {
+                float* dst = yout + (int64_t)cell * NO;
+#pragma unroll
+                for (int q = 0; q < NO; ++q) dst[q] = q < 9 ? y[q] : 0.0f;
             }
         }
-#pragma unroll
-        for (int q = 9; q < NO; ++q) dst[q] = 0.0f;
     }
 }
 
@@ -814,17 +940,23 @@ extern "C" int fp_lite_load(fp_ctx* c, fp_lite* n, const float* params, hipStrea
     return check_launch(c, "fp_lite_load");
 }
 
-static void infer(fp_ctx* c, const fp_lite* n, const double* mom, int mode, float* y, hipStream_t s) {
-    const int32_t cells_per_block = INF_BLOCK / 64 * 32;
-    const int grid = (c->ncell + cells_per_block - 1) / cells_per_block;
-    hipLaunchKernelGGL(lite_infer_kernel, dim3(grid), dim3(INF_BLOCK), 0, s, c->cfg, c->ncell, mom,
-                       (const double*)c->nvol, (const __bf16*)n->img, (const float*)n->sec, mode, y);
+// a workgroup per CU: eight waves (two per SIMD, which hide each other's latencies) once they
+// occupy every CU, else four (twice the workgroups)
+template <int MODE>
+static void infer(fp_ctx* c, const fp_lite* n, const double* mom, float* y, double* rec, int32_t* status, double relax,
+                  hipStream_t s) {
+    const bool wide = c->ncell > 128 * 256;
+    const int w = wide ? 8 : 4;
+    const int grid = std::min(256, (c->ncell + 32 * w - 1) / (32 * w));
+    hipLaunchKernelGGL((wide ? lite_infer_kernel<8, MODE> : lite_infer_kernel<4, MODE>), dim3(grid), dim3(64 * w), 0, s,
+                       c->cfg, c->ncell, mom, (const double*)c->nvol, (const __bf16*)n->img, (const float*)n->sec, y, rec,
+                       status, relax);
 }
 
 extern "C" int fp_lite_infer(fp_ctx* c, const fp_lite* n, const double* mom, float* y, hipStream_t s) {
     if (!c || !n || !mom || !y || n->ctx != c) return set_err(c, FP_EINVAL, "fp_lite_infer: bad argument");
     if (c->ncell == 0) return FP_OK;
-    infer(c, n, mom, 0, y, s);
+    infer<0>(c, n, mom, y, nullptr, nullptr, 1.0, s);
     return check_launch(c, "fp_lite_infer");
 }
 
@@ -837,7 +969,12 @@ extern "C" int fp_closure_lite(fp_ctx* c, const fp_lite* n, const double* mom, d
     if (c->cfg.moment_order == 3 && tol_abs != INFINITY)
         return set_err(c, FP_EINVAL, "fp_closure_lite: the check needs moments through fifth order");
     if (c->ncell == 0) return FP_OK;
-    infer(c, n, mom, 1, n->ybuf, s);
+    // third-order records have no system to check or to fall back on: one kernel
+    if (c->cfg.moment_order == 3) {
+        infer<2>(c, n, mom, nullptr, rec, status, relax, s);
+        return check_launch(c, "fp_closure_lite");
+    }
+    infer<1>(c, n, mom, n->ybuf, nullptr, nullptr, 1.0, s);
     const int rc = check_launch(c, "fp_closure_lite (network)");
     if (rc) return rc;
     return launch_closure_nn(c, n->ybuf, n->sec + SEC_ID, tol_abs, tol_rel, relax, mom, rec, status, s);
