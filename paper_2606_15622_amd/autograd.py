@@ -23,9 +23,10 @@ class ExactClosure(torch.autograd.Function):
         n = vx.shape[0]
         p = _view(ctx, vx, vy, vz, n)
         nc = ctx.ncell
-        mom = torch.zeros((nc, F.MOM_STRIDE), dtype=torch.float64, device=vx.device)
-        rec = torch.zeros((nc, F.REC_STRIDE), dtype=torch.float64, device=vx.device)
-        st = torch.zeros(nc, dtype=torch.int32, device=vx.device)
+        # the kernels write every entry of every cell: nothing is cleared first
+        mom = torch.empty((nc, F.MOM_STRIDE), dtype=torch.float64, device=vx.device)
+        rec = torch.empty((nc, F.REC_STRIDE), dtype=torch.float64, device=vx.device)
+        st = torch.empty(nc, dtype=torch.int32, device=vx.device)
         ctx.moments(p, offsets, mom)
         ctx.closure_solve(mom, rec, st)
         fctx.ctx = ctx
@@ -37,14 +38,14 @@ class ExactClosure(torch.autograd.Function):
         vx, vy, vz, offsets, mom, rec = fctx.saved_tensors
         ctx = fctx.ctx
         nc = ctx.ncell
-        ybar = torch.zeros((nc, F.REC_STRIDE), dtype=torch.float64, device=vx.device)
-        ybar[:, :9] = gy
-        mombar = torch.zeros((nc, F.MOM_STRIDE), dtype=torch.float64, device=vx.device)
+        ybar = torch.empty((nc, F.REC_STRIDE), dtype=torch.float64, device=vx.device)
+        ybar[:, :9] = gy   # the other entries are not read
+        mombar = torch.empty((nc, F.MOM_STRIDE), dtype=torch.float64, device=vx.device)
         ctx.closure_solve_backward(mom, rec, ybar, mombar)
         n = vx.shape[0]
-        gx = torch.zeros(n, dtype=torch.float64, device=vx.device)
-        gyy = torch.zeros_like(gx)
-        gz = torch.zeros_like(gx)
+        # zero for particles that no cell of offsets holds (a tensor each: a gradient that is
+        # kept holds no more than itself)
+        gx, gyy, gz = (torch.zeros(n, dtype=torch.float64, device=vx.device) for _ in range(3))
         ctx.moments_backward(_view(ctx, vx, vy, vz, n), offsets, mom, mombar, gx, gyy, gz)
         return gx.to(vx.dtype), gyy.to(vy.dtype), gz.to(vz.dtype), None, None
 
@@ -57,6 +58,5 @@ def _view(ctx, vx, vy, vz, n):
     p.x = vx            # positions are not read by the moment kernels
     p.y = None
     p.vx, p.vy, p.vz = vx, vy, vz
-    p.pid = torch.zeros(1, dtype=torch.int32, device=vx.device)
-    p.key = p.pid
+    p.pid = p.key = vx  # neither are ids and keys
     return p

@@ -190,12 +190,15 @@ def make_config(w: dict, capacity: int) -> FPConfig:
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    """The raw handle of a torch stream; by default of the current device's current one (what
+    torch.cuda.current_stream().cuda_stream is, without the Python object around it)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class Particles:
@@ -235,14 +238,9 @@ class Particles:
         return p
 
     def struct(self):
-        s = FPParticles()
-        s.x, s.vx, s.vy, s.vz = (t.data_ptr() for t in (self.x, self.vx, self.vy, self.vz))
-        s.y = self.y.data_ptr() if self.y is not None else None
-        s.pid, s.key = self.pid.data_ptr(), self.key.data_ptr()
-        s.n = self.n
-        s.n_dev = self.n_dev.data_ptr() if self.n_dev is not None else None
-        s.capacity = self.capacity
-        return s
+        return FPParticles(self.x.data_ptr(), _ptr(self.y), self.vx.data_ptr(), self.vy.data_ptr(),
+                           self.vz.data_ptr(), self.pid.data_ptr(), self.key.data_ptr(), self.n,
+                           _ptr(self.n_dev), self.capacity)
 
     def count(self):
         """The particle count (a host read of the device word when there is one)."""
