@@ -877,7 +877,6 @@ __global__ __launch_bounds__(BIN_BLOCK) void rebin_gather_kernel(
 // two moment passes.  Its workgroups are one wave (GM_BLOCK lanes, 64 / G cells, or one
 // cell of 64 lanes): the group's barriers (far staging, bucket prefix, slot read-back, the
 // moment reduction in LDS) then wait for the wave itself and never for other cells.
-constexpr int GM_U = 4;
 constexpr int GM_BLOCK = 64;
 
 template <typename T, int G, int NVX, int BLK = GM_BLOCK>
@@ -892,6 +891,9 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
     if (n_dev) n = *n_dev;
     if (kept && blockIdx.x == 0 && threadIdx.x == 0) *kept = offsets[ncell];
     constexpr int GROUPS = BLK / G;
+    // positions per lane and round: at 32 lanes one more, so that a cell of 100 particles and
+    // the shift to an aligned slot (below) still take one round
+    constexpr int GM_U = G >= 32 ? 5 : 4;
     __shared__ int32_t s_run[GROUPS][9][4];   // start in bidx, length, far before, range start
     __shared__ int32_t s_pre[GROUPS][10];     // bucket starts in the cell's concatenation
     __shared__ double s_samp[GROUPS][14];     // the cells' time-average sums
@@ -1003,40 +1005,40 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
         fb = s_run[grp][t][2];
         j = ld_off(bidx, s_run[grp][t][0] + q - s_pre[grp][t]);
     };
-    // one round: U positions per lane, all loads first; velocities returned
+    // one round: GM_U positions per lane, all loads first (without a branch between them, so
+    // that they go out together: 626 -> 616 us), then the stores; velocities returned
     auto round = [&](int32_t q0, T (&ox)[GM_U], T (&oy)[GM_U], T (&oz)[GM_U])
                      __attribute__((always_inline)) {
         int32_t src[GM_U], dst[GM_U];
 #pragma unroll
         for (int u = 0; u < GM_U; ++u) {
+            // positions beyond the last take the last one's loads and no stores
             const int32_t q = q0 + u * G + lg;
-            src[u] = -1;
-            dst[u] = -1;
-            if (q < nk) {
-                int32_t fb;
-                lookup(q, src[u], fb);
-                dst[u] = base + q + fb;
-            }
+            int32_t fb;
+            lookup(max(min(q, nk - 1), 0), src[u], fb);
+            dst[u] = q >= 0 && q < nk ? base + q + fb : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < GM_U; ++u) {
+            if (src[u] < 0) dst[u] = -1;
+            src[u] = max(src[u], 0);
         }
         T rx[GM_U], ry[GM_U];
         uint32_t rp[GM_U];
 #pragma unroll
         for (int u = 0; u < GM_U; ++u) {
-            ox[u] = oy[u] = oz[u] = (T)0;
-            if (src[u] >= 0) {
-                const int32_t j = src[u];
-                rx[u] = ld_off(r.sx, j);
-                ry[u] = r.sy ? ld_off(r.sy, j) : (T)0;
-                ox[u] = ld_off(r.svx, j);
-                oy[u] = ld_off(r.svy, j);
-                oz[u] = ld_off(r.svz, j);
-                rp[u] = ld_off(r.spid, j);
-            }
+            const int32_t j = src[u];
+            rx[u] = ld_off(r.sx, j);
+            ry[u] = r.sy ? ld_off(r.sy, j) : (T)0;
+            ox[u] = ld_off(r.svx, j);
+            oy[u] = ld_off(r.svy, j);
+            oz[u] = ld_off(r.svz, j);
+            rp[u] = ld_off(r.spid, j);
         }
 #pragma unroll
         for (int u = 0; u < GM_U; ++u) {
             const int32_t d = dst[u];
-            if (src[u] >= 0 && d >= 0 && d < lim) {
+            if (d >= 0 && d < lim) {
                 st_off(r.dx, d, rx[u]);
                 if (r.dy) st_off(r.dy, d, ry[u]);
                 st_off(r.dvx, d, ox[u]);
@@ -1053,10 +1055,16 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
     T kvx[GM_U], kvy[GM_U], kvz[GM_U];
 #pragma unroll
     for (int u = 0; u < GM_U; ++u) kvx[u] = kvy[u] = kvz[u] = (T)0;
-    for (int32_t q0 = 0; q0 < nk; q0 += G * GM_U) {
+    // without far arrivals the rounds start at the slot aligned to the group's lanes at or
+    // before the cell's first: every store of a group then writes whole cache lines but for
+    // the cell's ends, instead of two halves of lines each (stores are a third of the
+    // kernel: 626 -> 600 us for the re-sort of 2e7 particles; with four positions a lane, one
+    // round in six did not cover its cell and nothing was gained: 622)
+    const int32_t off = nf == 0 ? base & (G - 1) : 0;
+    for (int32_t q0 = nk > 0 ? -off : 0; q0 < nk; q0 += G * GM_U) {   // an empty cell loads nothing
         T tx[GM_U], ty[GM_U], tz[GM_U];
         round(q0, tx, ty, tz);
-        if (q0 == 0) {
+        if (q0 == -off) {
 #pragma unroll
             for (int u = 0; u < GM_U; ++u) {
                 kvx[u] = tx[u];
@@ -1082,14 +1090,14 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
     // barrier makes the group's writes visible to all of its lanes
     __syncthreads();
     const int32_t ncnt = in ? (int32_t)min((int64_t)nk + (f1 - f0), lim - base) : 0;
-    // register path (group-uniform): slot q of the cell is position q, held by lane q % G
-    // as round value q / G -- the same values in the same per-lane order as the slots
-    const bool regs = nf == 0 && ncnt == nk && nk <= G * GM_U;
+    // register path (group-uniform): slot q of the cell is position q, held by lane
+    // (q + off) % G as round value (q + off) / G
+    const bool regs = nf == 0 && ncnt == nk && nk + off <= G * GM_U;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     if (regs) {
 #pragma unroll
         for (int u = 0; u < GM_U; ++u)
-            if (u * G + lg < ncnt) {
+            if (u * G + lg >= off && u * G + lg - off < ncnt) {
                 s0 += (double)kvx[u];
                 s1 += (double)kvy[u];
                 s2 += (double)kvz[u];
@@ -1112,7 +1120,7 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
     if (regs) {
 #pragma unroll
         for (int u = 0; u < GM_U; ++u)
-            if (u * G + lg < ncnt)
+            if (u * G + lg >= off && u * G + lg - off < ncnt)
                 mom_accum<NVX>((double)kvx[u] - U0, (double)kvy[u] - U1, (double)kvz[u] - U2, acc);
     } else {
         for (int32_t q = lg; q < ncnt; q += G)
