@@ -82,6 +82,11 @@ namespace fpg {
 int set_err(fp_ctx* c, int code, const std::string& msg);
 int check_launch(fp_ctx* c, const char* what);
 
+// a ^ b ^ c in one instruction (gfx950's three-input bit operation, truth table 0x96)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // ---- Philox4x32-10 (Salmon et al., SC'11) -------------------------------------------------
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
 #pragma unroll
@@ -92,8 +97,8 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
         }
         const uint64_t p0 = (uint64_t)0xD2511F53u * c.x;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c.z;
-        c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k.x, (uint32_t)p1,
-                       (uint32_t)(p0 >> 32) ^ c.w ^ k.y, (uint32_t)p0);
+        c = make_uint4(xor3((uint32_t)(p1 >> 32), c.y, k.x), (uint32_t)p1,
+                       xor3((uint32_t)(p0 >> 32), c.w, k.y), (uint32_t)p0);
     }
     return c;
 }
@@ -156,10 +161,9 @@ __device__ __forceinline__ void normals3f(uint4 r, float& z0, float& z1, float& 
 // ---- cell key from a stored position (double, no contraction) --------------------------
 __device__ __forceinline__ int32_t axis_cell(double pos, double origin, double inv_h,
                                              int32_t n) {
+    // into [0, n - 1] before the conversion (NaN: 0)
     const double f = floor(__dmul_rn(__dsub_rn(pos, origin), inv_h));
-    if (!(f >= 0.0)) return 0;
-    if (f > (double)(n - 1)) return n - 1;
-    return (int32_t)f;
+    return (int32_t)fmin(fmax(f, 0.0), (double)(n - 1));
 }
 
 // ---- cross-lane sums inside aligned groups of G lanes (result in every lane) -----------
@@ -182,6 +186,37 @@ __device__ __forceinline__ double group_sum(double v) {
     if constexpr (G >= 32) v += __shfl_xor(v, 16, 64);
     if constexpr (G >= 64) v += __shfl_xor(v, 32, 64);
     return v;
+}
+
+// s[0..3] summed over aligned groups of G >= 4 lanes, every lane receiving all four sums: the
+// same additions as four group_sum calls (the same bits) with half the vector work.  The
+// first two exchanges halve what a lane carries (lane l keeps sum l % 4 of its quad), the wider
+// ones go through the LDS crossbar (no vector instruction), and quads broadcast at the end.
+template <int XOR>
+__device__ __forceinline__ double swizzle_xor_d(double v) {
+    if constexpr (XOR == 32) {
+        return __shfl_xor(v, 32, 64);
+    } else {
+        constexpr int P = (XOR << 10) | 0x1F;
+        return __hiloint2double(__builtin_amdgcn_ds_swizzle(__double2hiint(v), P),
+                                __builtin_amdgcn_ds_swizzle(__double2loint(v), P));
+    }
+}
+template <int G>
+__device__ __forceinline__ void group_sum4(double (&s)[4]) {
+    static_assert(G >= 4, "G");
+    const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+    const double a = (b0 ? s[1] : s[0]) + dpp_d<0xB1>(b0 ? s[0] : s[1]);
+    const double c = (b0 ? s[3] : s[2]) + dpp_d<0xB1>(b0 ? s[2] : s[3]);
+    double t = (b1 ? c : a) + dpp_d<0x4E>(b1 ? a : c);
+    if constexpr (G >= 8) t += swizzle_xor_d<4>(t);
+    if constexpr (G >= 16) t += swizzle_xor_d<8>(t);
+    if constexpr (G >= 32) t += swizzle_xor_d<16>(t);
+    if constexpr (G >= 64) t += swizzle_xor_d<32>(t);
+    s[0] = dpp_d<0x00>(t);
+    s[1] = dpp_d<0x55>(t);
+    s[2] = dpp_d<0xAA>(t);
+    s[3] = dpp_d<0xFF>(t);
 }
 
 // Workgroups are handed to the 8 XCDs (each with its own L2) round robin.  xcd_block

@@ -309,7 +309,7 @@ __global__ __launch_bounds__(ST_BLOCK) void collide_kernel(
     T* __restrict__ py, T* __restrict__ pvx, T* __restrict__ pvy, T* __restrict__ pvz,
     const uint32_t* __restrict__ ppid, int32_t* __restrict__ pkey, uint32_t step_arg, int move,
     const uint32_t* __restrict__ stepp, int32_t* __restrict__ pend, int32_t* __restrict__ plist,
-    uint32_t* __restrict__ stepc, const int32_t* __restrict__ kmap) {
+    uint32_t* __restrict__ stepc, const int32_t* __restrict__ kmap, double inv_dx, double inv_dy) {
     const uint32_t step = stepp ? stepp[0] : step_arg;
     if (stepc && blockIdx.x == 0 && threadIdx.x == 0) stepc[0] = step;   // for flight_rest
     const int64_t gt = (int64_t)blockIdx.x * ST_BLOCK + threadIdx.x;
@@ -360,11 +360,11 @@ __global__ __launch_bounds__(ST_BLOCK) void collide_kernel(
         if (j < na) {
             const int32_t p = b + j;
             if (move) {
-                xk[k] = px[p];
-                yk[k] = TWO_D ? py[p] : (T)0;
+                xk[k] = ld_off(px, p);
+                yk[k] = TWO_D ? ld_off(py, p) : (T)0;
             }
             T cs[3], nn, cn;
-            collide_one<T>(q, pvx[p], pvy[p], pvz[p], draw(g.seed, ppid[p], step, PURPOSE_COLLISION, 0),
+            collide_one<T>(q, ld_off(pvx, p), ld_off(pvy, p), ld_off(pvz, p), draw(g.seed, ld_off(ppid, p), step, PURPOSE_COLLISION, 0),
                            cs, nn, cn);
             cs0[k] = cs[0]; cs1[k] = cs[1]; cs2[k] = cs[2];
             const double d0 = cs[0], d1 = cs[1], d2 = cs[2];
@@ -377,19 +377,23 @@ __global__ __launch_bounds__(ST_BLOCK) void collide_kernel(
     for (int32_t j = lg + K * G; j < na; j += G) {
         const int32_t p = b + j;
         T cs[3], nn, cn;
-        collide_one<T>(q, pvx[p], pvy[p], pvz[p], draw(g.seed, ppid[p], step, PURPOSE_COLLISION, 0),
+        collide_one<T>(q, ld_off(pvx, p), ld_off(pvy, p), ld_off(pvz, p), draw(g.seed, ld_off(ppid, p), step, PURPOSE_COLLISION, 0),
                        cs, nn, cn);
-        pvx[p] = cs[0]; pvy[p] = cs[1]; pvz[p] = cs[2];
+        st_off(pvx, p, cs[0]); st_off(pvy, p, cs[1]); st_off(pvz, p, cs[2]);
         const double d0 = cs[0], d1 = cs[1], d2 = cs[2];
         s0 += d0; s1 += d1; s2 += d2;
         if (exact) s3 = fma(d0, d0, fma(d1, d1, fma(d2, d2, s3)));
         else { s3 += (double)nn; s4 += (double)cn; }
     }
-    s0 = group_sum<G>(s0);
-    s1 = group_sum<G>(s1);
-    s2 = group_sum<G>(s2);
-    s3 = group_sum<G>(s3);
-    s4 = group_sum<G>(s4);
+    {
+        double s[4] = {s0, s1, s2, s3};
+        group_sum4<G>(s);
+        s0 = s[0];
+        s1 = s[1];
+        s2 = s[2];
+        s3 = s[3];
+    }
+    if (!exact) s4 = group_sum<G>(s4);
 
     T cb[3] = {0, 0, 0}, sc = 1;
     if (active) {
@@ -414,37 +418,39 @@ __global__ __launch_bounds__(ST_BLOCK) void collide_kernel(
     // or body in reach) is decided here; a particle that may meet a wall or the body gets
     // its new velocity stored and takes the full flight in flight_rest_kernel, which keeps
     // the FP64 re-emission code (and its registers) out of this kernel.
-    const Walls W = make_walls(g);
-    const double inv_dx = 1.0 / g.dx, inv_dy = 1.0 / g.dy;
+    const double xlo = g.x0, xhi = g.x0 + g.lx, ylo = g.y0, yhi = g.y0 + g.ly;
     auto store_done = [&](int32_t p, double x, double y, T v0, T v1, T v2, bool gone) {
-        px[p] = (T)x;
-        if (TWO_D) py[p] = (T)y;
-        pvx[p] = v0; pvy[p] = v1; pvz[p] = v2;
-        pkey[p] = gone ? ncell : cell_key<TWO_D>(g, x, y, inv_dx, inv_dy, kmap);
+        st_off(px, p, (T)x);
+        if (TWO_D) st_off(py, p, (T)y);
+        st_off(pvx, p, v0); st_off(pvy, p, v1); st_off(pvz, p, v2);
+        st_off(pkey, p, gone ? ncell : cell_key<TWO_D>(g, x, y, inv_dx, inv_dy, kmap));
     };
     // returns false when the full flight is still to do (velocity already stored)
     auto finish_fast = [&](int32_t p, T v0, T v1, T v2, T xo, T yo) -> bool {
         if (!move) {
-            pvx[p] = v0; pvy[p] = v1; pvz[p] = v2;
+            st_off(pvx, p, v0); st_off(pvy, p, v1); st_off(pvz, p, v2);
             return true;
         }
         const double x0 = (double)xo, y0 = TWO_D ? (double)yo : 0.0;
         const double w0 = (double)v0, w1 = (double)v1;
         const double ex = __dadd_rn(x0, __dmul_rn(w0, g.dt));
         const double ey = TWO_D ? __dadd_rn(y0, __dmul_rn(w1, g.dt)) : 0.0;
-        bool plain, gone = false;
+        // plain may be false for a flight that meets nothing (flight_rest then flies it alike),
+        // never true for one that might
+        const bool inside = ex >= xlo && ex <= xhi && (!TWO_D || (ey >= ylo && ey <= yhi));
+        bool plain = inside, gone = false;
         if constexpr (GEOM == FP_CYLINDER2D) {
-            // no hit is possible when the body is out of reach by a wide margin
-            const double dxc = x0 - g.circle[0], dyc = y0 - g.circle[1];
-            const double reach = g.circle[2] + sqrt(w0 * w0 + w1 * w1) * g.dt;
-            plain = dxc * dxc + dyc * dyc > reach * reach * (1.0 + 1e-6) + 1e-300;
-            gone = ex < g.x0 || ex > g.x0 + g.lx || ey < g.y0 || ey > g.y0 + g.ly;
-        } else {
-            plain = !((ex < W.lo[0] && w0 < 0.0) || (ex > W.hi[0] && w0 > 0.0) ||
-                      (TWO_D && ((ey < W.lo[1] && w1 < 0.0) || (ey > W.hi[1] && w1 > 0.0))));
+            // no hit is possible when the body is out of reach, in single precision with a
+            // margin far beyond its rounding
+            const float dxc = (float)(x0 - g.circle[0]), dyc = (float)(y0 - g.circle[1]);
+            const float u0 = (float)w0, u1 = (float)w1;
+            const float reach = (float)g.circle[2] +
+                                __builtin_amdgcn_sqrtf(__builtin_fmaf(u0, u0, u1 * u1)) * (float)g.dt;
+            plain = __builtin_fmaf(dxc, dxc, dyc * dyc) > reach * reach * 1.0001f + 1e-30f;
+            gone = !inside;
         }
         if (!plain) {
-            pvx[p] = v0; pvy[p] = v1; pvz[p] = v2;
+            st_off(pvx, p, v0); st_off(pvy, p, v1); st_off(pvz, p, v2);
             return false;
         }
         store_done(p, st_round(ex, f32), TWO_D ? st_round(ey, f32) : 0.0, v0, v1, v2, gone);
@@ -472,18 +478,18 @@ __global__ __launch_bounds__(ST_BLOCK) void collide_kernel(
         if (j < n) {
             const int32_t p = b + j;
             // the inactive cells' particles (na = 0) were not prefetched
-            const T xo = !move ? (T)0 : (active ? xk[k] : px[p]);
-            const T yo = !move || !TWO_D ? (T)0 : (active ? yk[k] : py[p]);
+            const T xo = !move ? (T)0 : (active ? xk[k] : ld_off(px, p));
+            const T yo = !move || !TWO_D ? (T)0 : (active ? yk[k] : ld_off(py, p));
             if (active) finish(p, newv(cs0[k], 0), newv(cs1[k], 1), newv(cs2[k], 2), xo, yo);
-            else finish(p, pvx[p], pvy[p], pvz[p], xo, yo);
+            else finish(p, ld_off(pvx, p), ld_off(pvy, p), ld_off(pvz, p), xo, yo);
         }
     }
     for (int32_t j = lg + K * G; j < n; j += G) {
         const int32_t p = b + j;
-        const T xo = move ? px[p] : (T)0;
-        const T yo = move && TWO_D ? py[p] : (T)0;
-        if (active) finish(p, newv(pvx[p], 0), newv(pvy[p], 1), newv(pvz[p], 2), xo, yo);
-        else finish(p, pvx[p], pvy[p], pvz[p], xo, yo);
+        const T xo = move ? ld_off(px, p) : (T)0;
+        const T yo = move && TWO_D ? ld_off(py, p) : (T)0;
+        if (active) finish(p, newv(ld_off(pvx, p), 0), newv(ld_off(pvy, p), 1), newv(ld_off(pvz, p), 2), xo, yo);
+        else finish(p, ld_off(pvx, p), ld_off(pvy, p), ld_off(pvz, p), xo, yo);
     }
     if (move && in && lg == 0) pend[cell] = npend;   // lane 0 takes part in every round
 }
@@ -604,7 +610,7 @@ static void collide_launch(fp_ctx* c, fp_particles* p, const int32_t* off, const
     hipLaunchKernelGGL((collide_kernel<T, G, K, GEOM>), dim3(grid), dim3(ST_BLOCK), 0, s,
                        c->cfg, c->ncell, off, mom, rec, (T*)p->x, (T*)p->y, (T*)p->vx, (T*)p->vy,
                        (T*)p->vz, p->pid, p->key, step, move, stepp, c->pend, c->bidx,
-                       adv ? c->stepc : nullptr, (const int32_t*)c->leafmap);
+                       adv ? c->stepc : nullptr, (const int32_t*)c->leafmap, 1.0 / c->cfg.dx, 1.0 / c->cfg.dy);
     if (move) {
         const int fr = c->ncell <= 65536 ? 2 : 4;
         const int32_t per_block = FR_BLOCK / 64 * fr;
