@@ -872,8 +872,9 @@ __global__ __launch_bounds__(BIN_BLOCK) void rebin_gather_kernel(
 // moment reduction in LDS) then wait for the wave itself and never for other cells.
 constexpr int GM_BLOCK = 64;
 
+// (in FP64 five positions a lane take 134 registers, one wave fewer per SIMD: bounded to 128)
 template <typename T, int G, int NVX, int BLK = GM_BLOCK>
-__global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
+__global__ __launch_bounds__(BLK, sizeof(T) == 8 && G >= 32 ? 4 : 1) void rebin_gather_mom_kernel(
     int32_t ncell, int32_t nx, int32_t ny, int64_t n, const int64_t* __restrict__ n_dev,
     int64_t* __restrict__ kept, int64_t cap,
     const int32_t* __restrict__ src_off, const int32_t* __restrict__ bend,
@@ -998,13 +999,14 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
         fb = s_run[grp][t][2];
         j = ld_off(bidx, s_run[grp][t][0] + q - s_pre[grp][t]);
     };
-    // one round: GM_U positions per lane, all loads first (without a branch between them, so
-    // that they go out together: 626 -> 616 us), then the stores; velocities returned
-    auto round = [&](int32_t q0, T (&ox)[GM_U], T (&oy)[GM_U], T (&oz)[GM_U])
+    // one round: V of the GM_U positions per lane, all loads first (without a branch between
+    // them, so that they go out together: 626 -> 616 us), then the stores; velocities returned
+    auto round = [&](auto positions, int32_t q0, T (&ox)[GM_U], T (&oy)[GM_U], T (&oz)[GM_U])
                      __attribute__((always_inline)) {
-        int32_t src[GM_U], dst[GM_U];
+        constexpr int V = decltype(positions)::value;
+        int32_t src[V], dst[V];
 #pragma unroll
-        for (int u = 0; u < GM_U; ++u) {
+        for (int u = 0; u < V; ++u) {
             // positions beyond the last take the last one's loads and no stores
             const int32_t q = q0 + u * G + lg;
             int32_t fb;
@@ -1012,14 +1014,14 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
             dst[u] = q >= 0 && q < nk ? base + q + fb : -1;
         }
 #pragma unroll
-        for (int u = 0; u < GM_U; ++u) {
+        for (int u = 0; u < V; ++u) {
             if (src[u] < 0) dst[u] = -1;
             src[u] = max(src[u], 0);
         }
-        T rx[GM_U], ry[GM_U];
-        uint32_t rp[GM_U];
+        T rx[V], ry[V];
+        uint32_t rp[V];
 #pragma unroll
-        for (int u = 0; u < GM_U; ++u) {
+        for (int u = 0; u < V; ++u) {
             const int32_t j = src[u];
             rx[u] = ld_off(r.sx, j);
             ry[u] = r.sy ? ld_off(r.sy, j) : (T)0;
@@ -1029,7 +1031,7 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
             rp[u] = ld_off(r.spid, j);
         }
 #pragma unroll
-        for (int u = 0; u < GM_U; ++u) {
+        for (int u = 0; u < V; ++u) {
             const int32_t d = dst[u];
             if (d >= 0 && d < lim) {
                 st_off(r.dx, d, rx[u]);
@@ -1052,17 +1054,27 @@ __global__ __launch_bounds__(BLK) void rebin_gather_mom_kernel(
     // before the cell's first: every store of a group then writes whole cache lines but for
     // the cell's ends, instead of two halves of lines each (stores are a third of the
     // kernel: 626 -> 600 us for the re-sort of 2e7 particles; with four positions a lane, one
-    // round in six did not cover its cell and nothing was gained: 622)
-    const int32_t off = nf == 0 ? base & (G - 1) : 0;
-    for (int32_t q0 = nk > 0 ? -off : 0; q0 < nk; q0 += G * GM_U) {   // an empty cell loads nothing
-        T tx[GM_U], ty[GM_U], tz[GM_U];
-        round(q0, tx, ty, tz);
-        if (q0 == -off) {
+    // round in six did not cover its cell and nothing was gained: 622).  Cells of at most one
+    // position a lane have nothing to gain from it, and neither they nor those that two cover
+    // take the loads of GM_U (decided for a wave's cells together): at 28 particles per cell
+    // and 32 lanes (a loop of 14 000 FP64 cells) two steps take 156 us instead of 161
+    const bool one = __all(nk <= G);
+    const int32_t off = nf == 0 && !one ? base & (G - 1) : 0;
+    if (one) {
+        if (nk > 0) round(std::integral_constant<int, 1>{}, 0, kvx, kvy, kvz);
+    } else if (__all(nk + off <= 2 * G)) {
+        if (nk > 0) round(std::integral_constant<int, 2>{}, -off, kvx, kvy, kvz);
+    } else {
+        for (int32_t q0 = nk > 0 ? -off : 0; q0 < nk; q0 += G * GM_U) {   // an empty cell loads nothing
+            T tx[GM_U], ty[GM_U], tz[GM_U];
+            round(std::integral_constant<int, GM_U>{}, q0, tx, ty, tz);
+            if (q0 == -off) {
 #pragma unroll
-            for (int u = 0; u < GM_U; ++u) {
-                kvx[u] = tx[u];
-                kvy[u] = ty[u];
-                kvz[u] = tz[u];
+                for (int u = 0; u < GM_U; ++u) {
+                    kvx[u] = tx[u];
+                    kvy[u] = ty[u];
+                    kvz[u] = tz[u];
+                }
             }
         }
     }
