@@ -68,8 +68,8 @@ __global__ __launch_bounds__(BIN_BLOCK) void bin_wave_kernel(
 // 13.2 + 4.6 + 10.4.
 constexpr int SCAN_BLOCK = 256, SCAN_MAX = 8191, SCAN_MAX_CELLS = SCAN_MAX * SCAN_BLOCK * 16;
 
-template <int BLOCK>
-__device__ __forceinline__ int32_t wg_excl_scan(int32_t v, int32_t* sh, int32_t& total);
+template <int BLOCK, int N>
+__device__ __forceinline__ void wg_excl_scan_n(int32_t (&v)[N], int32_t (*sh)[N], int32_t (&total)[N]);
 
 // a[j st], b[j st]: two arrays, or (st = 2) the two words of interleaved pairs
 template <int ITEMS>
@@ -107,28 +107,24 @@ template <int ITEMS>
 __global__ __launch_bounds__(SCAN_BLOCK) void scan_final_kernel(
     const int32_t* __restrict__ a, const int32_t* __restrict__ b, int32_t st, int32_t len,
     const int32_t* __restrict__ bsum, int32_t* __restrict__ outa, int32_t* __restrict__ outb) {
-    __shared__ int32_t sh[SCAN_BLOCK / 64 + 1];
+    __shared__ int32_t sh[SCAN_BLOCK / 64][4];
     const int64_t base = (int64_t)blockIdx.x * (SCAN_BLOCK * ITEMS) + (int64_t)threadIdx.x * ITEMS;
     int32_t va[ITEMS], vb[ITEMS];
-    int32_t sa = 0, sb = 0;
+    int32_t s[4] = {0, 0, 0, 0}, t[4];   // own items; totals of the tiles before this one
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t j = base + i;
         va[i] = j < len ? a[j * st] : 0;
         vb[i] = j < len ? b[j * st] : 0;
-        sa += va[i];
-        sb += vb[i];
+        s[0] += va[i];
+        s[1] += vb[i];
     }
-    // the totals of the tiles before this one, added to the thread's own start
-    int32_t pa = 0, pb = 0, ta, tb, ca, cb;
     for (int32_t j = threadIdx.x; j < (int32_t)blockIdx.x; j += SCAN_BLOCK) {
-        pa += bsum[j];
-        pb += bsum[8192 + j];
+        s[2] += bsum[j];
+        s[3] += bsum[8192 + j];
     }
-    wg_excl_scan<SCAN_BLOCK>(pa, sh, ca);
-    wg_excl_scan<SCAN_BLOCK>(pb, sh, cb);
-    int32_t ea = wg_excl_scan<SCAN_BLOCK>(sa, sh, ta) + ca;
-    int32_t eb = wg_excl_scan<SCAN_BLOCK>(sb, sh, tb) + cb;
+    wg_excl_scan_n<SCAN_BLOCK>(s, sh, t);
+    int32_t ea = s[0] + t[2], eb = s[1] + t[3];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t j = base + i;
@@ -140,8 +136,8 @@ __global__ __launch_bounds__(SCAN_BLOCK) void scan_final_kernel(
         eb += vb[i];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        outa[len] = ca + ta;
-        outb[len] = cb + tb;
+        outa[len] = t[2] + t[0];
+        outb[len] = t[3] + t[1];
     }
 }
 
@@ -397,33 +393,54 @@ __device__ __forceinline__ uint32_t group_incl_scan(uint32_t x, int lg) {
     return x;
 }
 
-// exclusive prefix sum over a workgroup of BLOCK threads (wave shuffles, then the wave
-// totals in LDS); sh holds BLOCK/64 + 1 ints; total receives the sum over the block
+// inclusive prefix sum over the lanes of a wave (DPP row shifts and row broadcasts)
+__device__ __forceinline__ int32_t row_incl_scan(int32_t x) {   // over each row of 16 lanes
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    return x;
+}
+__device__ __forceinline__ int32_t wave_incl_scan(int32_t x) {
+    x = row_incl_scan(x);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// exclusive prefix sums of N values over a workgroup of BLOCK <= 1024 threads, in place;
+// total: the sums over the block.  One LDS round for all of them: every wave scans the wave
+// totals in its own lanes.  (With one thread walking them while the others waited, and a round
+// for each value, the scan of 100 cells took 5.5 us instead of 3.2; two steps of 1e6 particles
+// on 1e4 cells 168 us instead of 162)
+template <int BLOCK, int N>
+__device__ __forceinline__ void wg_excl_scan_n(int32_t (&v)[N], int32_t (*sh)[N], int32_t (&total)[N]) {
+    constexpr int WAVES = BLOCK / 64;
+    static_assert(WAVES >= 1 && WAVES <= 16, "the wave totals fit one row of lanes");
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int32_t x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        x[i] = wave_incl_scan(v[i]);
+        if (lane == 63) sh[wv][i] = x[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int32_t t = row_incl_scan(lane < WAVES ? sh[lane][i] : 0);
+        total[i] = __builtin_amdgcn_readlane(t, WAVES - 1);
+        v[i] = (wv > 0 ? __builtin_amdgcn_readlane(t, max(wv - 1, 0)) : 0) + x[i] - v[i];
+    }
+    __syncthreads();
+}
+
+// one value; sh holds BLOCK / 64 ints
 template <int BLOCK>
 __device__ __forceinline__ int32_t wg_excl_scan(int32_t v, int32_t* sh, int32_t& total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int32_t x = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int32_t y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) sh[wv] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int32_t run = 0;
-        for (int i = 0; i < BLOCK / 64; ++i) {
-            const int32_t t = sh[i];
-            sh[i] = run;
-            run += t;
-        }
-        sh[BLOCK / 64] = run;
-    }
-    __syncthreads();
-    total = sh[BLOCK / 64];
-    const int32_t r = sh[wv] + x - v;
-    __syncthreads();
-    return r;
+    int32_t x[1] = {v}, t[1];
+    wg_excl_scan_n<BLOCK>(x, reinterpret_cast<int32_t(*)[1]>(sh), t);
+    total = t[0];
+    return x[0];
 }
 
 __device__ __forceinline__ void far_put(int32_t k, int32_t j, int64_t slot, int64_t cap,
@@ -471,7 +488,7 @@ __global__ __launch_bounds__(BIN_BLOCK) void rebin_count_kernel(
     int32_t* __restrict__ fcnt, int32_t* __restrict__ farn, uint64_t* __restrict__ flist,
     unsigned long long* __restrict__ errcount) {
     if (n_dev) n = *n_dev;
-    __shared__ int32_t sh[BIN_BLOCK / 64 + 1];
+    __shared__ int32_t sh[BIN_BLOCK / 64];
     __shared__ int32_t s_base;
     __shared__ int32_t s_next[BIN_BLOCK / G][9];
     const int lane = threadIdx.x & 63, grp = threadIdx.x / G;
@@ -645,32 +662,39 @@ __global__ __launch_bounds__(SSB) void rebin_small_scan_kernel(
     int32_t ncell, int64_t cap, const int32_t* __restrict__ cnt, const int32_t* __restrict__ fcnt,
     int32_t* __restrict__ offsets, int32_t* __restrict__ foff, const int32_t* __restrict__ farn,
     const uint64_t* __restrict__ flist, int32_t* __restrict__ fkey, int32_t* __restrict__ fsrc) {
-    __shared__ int32_t sh[SSB / 64 + 1];
+    __shared__ int32_t sh[SSB / 64][4];
     __shared__ int32_t s_foff[SSB], s_cur[SSB];
-    const int32_t k0 = blockIdx.x * SSB;
-    int32_t pa = 0, pb = 0;
+    const int32_t k0 = blockIdx.x * SSB, k = k0 + threadIdx.x;
+    // own counts; the counts of the earlier ranges (one branch per range for the whole
+    // workgroup, no wait between the loads)
+    int32_t s[4] = {0, 0, 0, 0}, t[4];
+    if (k < ncell) {
+        s[0] = cnt[k];
+        s[1] = fcnt[k];
+    }
+    int32_t la[SS_UR - 1], lb[SS_UR - 1];
 #pragma unroll
-    for (int u = 0; u < SS_UR; ++u) {
-        const int32_t k = u * SSB + threadIdx.x;
-        if (k < k0) {
-            pa += cnt[k];
-            pb += fcnt[k];
+    for (int u = 0; u < SS_UR - 1; ++u) {
+        la[u] = lb[u] = 0;
+        if (u < (int)blockIdx.x) {
+            la[u] = cnt[u * SSB + threadIdx.x];
+            lb[u] = fcnt[u * SSB + threadIdx.x];
         }
     }
-    int32_t ta, tb, sa, sb;
-    (void)wg_excl_scan<SSB>(pa, sh, ta);
-    (void)wg_excl_scan<SSB>(pb, sh, tb);
-    const int32_t k = k0 + threadIdx.x;
-    const int32_t va = k < ncell ? cnt[k] : 0, vb = k < ncell ? fcnt[k] : 0;
-    const int32_t ea = wg_excl_scan<SSB>(va, sh, sa) + ta;
-    const int32_t eb = wg_excl_scan<SSB>(vb, sh, sb) + tb;
+#pragma unroll
+    for (int u = 0; u < SS_UR - 1; ++u) {
+        s[2] += la[u];
+        s[3] += lb[u];
+    }
+    wg_excl_scan_n<SSB>(s, sh, t);
+    const int32_t ea = s[0] + t[2], eb = s[1] + t[3], sb = t[1];
     if (k < ncell) {
         offsets[k] = ea;
         foff[k] = eb;
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        offsets[ncell] = ta + sa;
-        foff[ncell] = tb + sb;
+        offsets[ncell] = t[2] + t[0];
+        foff[ncell] = t[3] + t[1];
     }
     if (sb == 0) return;    // no far arrivals in this range (block-uniform)
     s_foff[threadIdx.x] = eb;
