@@ -393,21 +393,6 @@ __device__ __forceinline__ uint32_t group_incl_scan(uint32_t x, int lg) {
     return x;
 }
 
-// inclusive prefix sum over the lanes of a wave (DPP row shifts and row broadcasts)
-__device__ __forceinline__ int32_t row_incl_scan(int32_t x) {   // over each row of 16 lanes
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
-    return x;
-}
-__device__ __forceinline__ int32_t wave_incl_scan(int32_t x) {
-    x = row_incl_scan(x);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-
 // exclusive prefix sums of N values over a workgroup of BLOCK <= 1024 threads, in place;
 // total: the sums over the block.  One LDS round for all of them: every wave scans the wave
 // totals in its own lanes.  (With one thread walking them while the others waited, and a round
@@ -421,13 +406,13 @@ __device__ __forceinline__ void wg_excl_scan_n(int32_t (&v)[N], int32_t (*sh)[N]
     int32_t x[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        x[i] = wave_incl_scan(v[i]);
+        x[i] = (int32_t)group_incl_scan<64>((uint32_t)v[i], lane);
         if (lane == 63) sh[wv][i] = x[i];
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const int32_t t = row_incl_scan(lane < WAVES ? sh[lane][i] : 0);
+        const int32_t t = (int32_t)group_incl_scan<16>(lane < WAVES ? (uint32_t)sh[lane][i] : 0u, lane & 15);
         total[i] = __builtin_amdgcn_readlane(t, WAVES - 1);
         v[i] = (wv > 0 ? __builtin_amdgcn_readlane(t, max(wv - 1, 0)) : 0) + x[i] - v[i];
     }
@@ -458,7 +443,15 @@ __device__ __forceinline__ int32_t bucket_len(const int32_t* __restrict__ bend, 
 
 // grid: ncell*G lanes for the old cells, then FAR_BLOCKS blocks for the ungrouped tail.
 // Far movers are appended to the list with one atomic per block (cells) or per wave
-// (tail) on its length: a single counter hit once per particle would serialise.
+// (tail) on its length.  These atomics on one address are what bounds the kernel as soon as
+// most blocks have a far mover: 10.6 ns each, whatever else runs, 66 us for the 6272 blocks of
+// 256 threads that 2e7 particles on 200 704 cells make.  Hence blocks of 1024 threads for more
+// than RC_SMALL lanes (93 -> 67 us; 1e6 particles on 1e4 cells 14.5 -> 11; the grid of 100
+// cells, 25 narrow blocks or 7 wide ones, 5.6 against 7.9 us the other way).  Persistent blocks
+// that collect far movers in LDS over several tiles: 69 and 13 us.
+// A lane takes a run of consecutive particles, and LDS counters of its own give a particle
+// its place: against a prefix sum over the group for every round of particles, and all keys
+// read again for the far movers, 113 -> 93 us.
 constexpr int FAR_BLOCKS = 64;
 
 // Order in which the gathers visit destination cells on a 2-D grid: column strips of
@@ -480,24 +473,34 @@ __device__ __forceinline__ int32_t strip_cell(int32_t t, int32_t nx, int32_t ny)
     return (r / w) * nx + full * STRIP + r % w;
 }
 
-template <int G>
-__global__ __launch_bounds__(BIN_BLOCK) void rebin_count_kernel(
+// entries of bidx that a wave of the count kernel puts together in LDS
+constexpr int RC_STAGE = 1024;
+// lanes up to which workgroups of 256 are taken (up to 512 of them)
+constexpr int64_t RC_SMALL = 512 * 256;
+// *p += 1 in LDS, old value returned
+__device__ __forceinline__ int32_t lds_inc(int32_t* p) {
+    return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+template <int G, int BLK>
+__global__ __launch_bounds__(BLK) void rebin_count_kernel(
     int32_t ncell, int32_t nx, int64_t n, const int64_t* __restrict__ n_dev, int64_t cap,
     int32_t cell_blocks, const int32_t* __restrict__ src_off, const int32_t* __restrict__ key,
     int32_t* __restrict__ bend, int32_t* __restrict__ bidx, int32_t* __restrict__ cnt,
     int32_t* __restrict__ fcnt, int32_t* __restrict__ farn, uint64_t* __restrict__ flist,
     unsigned long long* __restrict__ errcount) {
     if (n_dev) n = *n_dev;
-    __shared__ int32_t sh[BIN_BLOCK / 64];
+    __shared__ int32_t sh[BLK / 64];
     __shared__ int32_t s_base;
-    __shared__ int32_t s_next[BIN_BLOCK / G][9];
-    const int lane = threadIdx.x & 63, grp = threadIdx.x / G;
+    __shared__ int32_t s_pos[BLK / 64][10][64];   // the last row: no direction
+    __shared__ uint16_t s_stage[BLK / 64][RC_STAGE + 2];
+    const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
     if ((int32_t)blockIdx.x >= cell_blocks) {
         // particles after the grouped range: all take the general path
         const int64_t t0 = max((int64_t)src_off[ncell], (int64_t)0);
-        const int64_t stride = (int64_t)FAR_BLOCKS * BIN_BLOCK;
-        for (int64_t jb = t0 + (int64_t)(blockIdx.x - cell_blocks) * BIN_BLOCK; jb < n;
+        const int64_t stride = (int64_t)FAR_BLOCKS * BLK;
+        for (int64_t jb = t0 + (int64_t)(blockIdx.x - cell_blocks) * BLK; jb < n;
              jb += stride) {
             const int64_t j = jb + threadIdx.x;
             int32_t k = ncell;
@@ -517,134 +520,164 @@ __global__ __launch_bounds__(BIN_BLOCK) void rebin_count_kernel(
         }
         return;
     }
-    const int64_t gt = (int64_t)blockIdx.x * BIN_BLOCK + threadIdx.x;
+    const int64_t gt = (int64_t)blockIdx.x * BLK + threadIdx.x;
     const int32_t cell = (int32_t)(gt / G);
     const int lg = (int)(gt % G);
-    int c9[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     int32_t nfar = 0, b = 0, e = 0, cx = 0, rs = 0;
-    constexpr int KR = 4;
-    int32_t kfirst[KR];   // the keys of the first round, kept for the second pass
-#pragma unroll
-    for (int u = 0; u < KR; ++u) kfirst[u] = ncell;
     if (cell < ncell) {
         b = max(src_off[cell], 0);
         e = (int32_t)min((int64_t)src_off[cell + 1], n);
         cx = cell % nx;
         rs = cell - cx;
-        // branch-free: per round of KR particles the directions are counted in three words
-        // of three 10-bit fields (at most KR per field), unpacked once per round
-        int32_t nbad = 0;
-        for (int32_t j0 = b + lg; j0 < e; j0 += G * KR) {
-            int32_t kk[KR];
-#pragma unroll
-            for (int u = 0; u < KR; ++u) kk[u] = j0 + u * G < e ? key[j0 + u * G] : ncell;
-            if (j0 == b + lg)
-#pragma unroll
-                for (int u = 0; u < KR; ++u) kfirst[u] = kk[u];
-            uint32_t w[3] = {0u, 0u, 0u};
-#pragma unroll
-            for (int u = 0; u < KR; ++u) {
-                const int32_t k = kk[u];
-                const bool valid = k >= 0 && k < ncell;
-                nbad += (!valid && k != ncell) ? 1 : 0;
-                const int d = valid ? near_dir(k, rs, cx, nx) : -1;
-                nfar += (valid && d < 0) ? 1 : 0;
-                const int dw = d < 0 ? 3 : d / 3;
-                const uint32_t one = 1u << (10 * (d - 3 * dw));
-#pragma unroll
-                for (int q = 0; q < 3; ++q) w[q] += dw == q ? one : 0u;
-            }
-#pragma unroll
-            for (int i = 0; i < 9; ++i) c9[i] += (int)((w[i / 3] >> (10 * (i % 3))) & 1023u);
-        }
-        if (nbad) atomicAdd(errcount, (unsigned long long)nbad);
     }
-    // bucket starts inside the cell's range (prefix over directions), same in every lane
-    int32_t bst[9];
+    // lane lg takes the lg-th run of the cell's particles, so that a particle's rank among
+    // those of its direction is the count of the lanes before plus its lane's own so far
+    const int32_t chunk = (max(e - b, 0) + G - 1) / G, j0 = b + lg * chunk;
+    const int32_t mine = max(min(e - j0, chunk), 0);
+    int32_t(&pos)[10][64] = s_pos[threadIdx.x >> 6];   // this lane's column only
+    uint16_t* stage = s_stage[threadIdx.x >> 6];
+    // the wave's cells follow each other, so do their ranges of bidx: they are put together in
+    // LDS and written as one (else, only with crowded cells or a bad src_off, in place)
+    const int64_t cells_left = (int64_t)ncell - (gt - lane) / G;
+    const int32_t wb = __builtin_amdgcn_readfirstlane(b);
+    const int32_t we = cells_left > 0 ? __builtin_amdgcn_readlane(e, (int)min(cells_left * G, (int64_t)64) - 1) : wb;
+    const bool staged = we >= wb && we - wb <= RC_STAGE && __all(cell >= ncell || (b >= wb && b <= e && e <= we));
+#pragma unroll
+    for (int i = 0; i < 9; ++i) pos[i][lane] = 0;
+    // four keys of the run from r on, ncell (no destination) beyond it.  Read as one, up to
+    // three keys past the run, but for the last waves
+    struct Keys { int32_t k[4]; };
+    const bool wide = __all(j0 + (int64_t)mine + 4 <= n);
+    auto load4 = [&](int32_t r) __attribute__((always_inline)) {
+        Keys q = {{ncell, ncell, ncell, ncell}};
+        if (wide) {
+            const int32_t* p = key + (r < mine ? j0 + r : 0);
+            q = {{p[0], p[1], p[2], p[3]}};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q.k[u] = r + u < mine ? q.k[u] : ncell;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r + u < mine) q.k[u] = key[j0 + r + u];
+        }
+        return q;
+    };
+    // direction of a key, NONE for a far, deleted or invalid one
+    constexpr uint32_t NONE = 9;
+    auto direction = [&](int32_t k) __attribute__((always_inline)) {
+        const int32_t rel = k - rs;
+        const int32_t dy = (rel >= nx ? 1 : 0) - (rel < 0 ? 1 : 0);
+        const int32_t dx = rel - dy * nx - cx;
+        const bool near = (uint32_t)k < (uint32_t)ncell & rel >= -nx & rel < 2 * nx & (uint32_t)(dx + 1) < 3u;
+        return near ? (uint32_t)(3 * dy + dx + 4) : NONE;
+    };
+    // first pass: counts per direction; the directions of a lane's first sixteen particles
+    // are kept, four bits each
+    uint64_t kept = 0;
+    int32_t nbad = 0;
     {
-        int32_t acc = 0;
+        auto count4 = [&](const Keys& q, int32_t r) __attribute__((always_inline)) {
+            uint32_t quad = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int32_t k = q.k[u];
+                const uint32_t d = direction(k);
+                nbad += (uint32_t)k > (uint32_t)ncell ? 1 : 0;
+                nfar += ((uint32_t)k < (uint32_t)ncell && d == NONE) ? 1 : 0;
+                quad |= d << (4 * u);
+                lds_inc(&pos[d][lane]);
+            }
+            if (r < 16) kept |= (uint64_t)quad << (4 * r);
+        };
+        Keys q[4];   // all of the first sixteen on their way at once
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v == 0 || __any(4 * v < mine)) q[v] = load4(4 * v);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (__any(4 * v < mine)) count4(q[v], 4 * v);
+        for (int32_t r = 16; __any(r < mine); r += 4) count4(load4(r), r);
+    }
+    if (nbad) atomicAdd(errcount, (unsigned long long)nbad);
+    // the lane's next place in every bucket (from wb if staged): bucket starts inside the cell, then the
+    // lanes before
+    {
+        const int last = lane - lg + G - 1;
+        int32_t run = 0, t[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
-            c9[i] = group_sum_i<G>(c9[i]);
-            bst[i] = acc;
-            acc += c9[i];
-        }
-    }
-    if (cell < ncell) {
-        if (lg == 0) {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) bend[(int64_t)cell * 9 + i] = bst[i] + c9[i];
+            const int32_t c = pos[i][lane];
+            const int32_t incl = (int32_t)group_incl_scan<G>((uint32_t)c, lg);
+            t[i] = __shfl(incl, last, 64);
+            pos[i][lane] = (staged ? b - wb : b) + run + incl - c;
+            run += t[i];
+            if (cell < ncell && lg == i % G) bend[(int64_t)cell * 9 + i] = run;
         }
         // this cell's share of the destination counts (integer adds: order-free); lane lg
         // takes directions lg, lg + G, ... (groups may have fewer than 9 lanes)
-        for (int q = lg; q < 9; q += G) {
-            int32_t cnt_d = 0;
+        if (cell < ncell)
+            for (int q = lg; q < 9; q += G) {
+                int32_t cnt_d = 0;
 #pragma unroll
-            for (int i = 0; i < 9; ++i) cnt_d = q == i ? c9[i] : cnt_d;
-            if (cnt_d > 0) atomicAdd(&cnt[cell + (q / 3 - 1) * nx + (q % 3 - 1)], cnt_d);
-        }
-        // second pass: source indices into the buckets, in source order.  Per round of
-        // G particles the rank of a particle among those of its direction is a group
-        // prefix sum of one-hot counters (three words of three 10-bit fields; at most
-        // G <= 64 per field); the next free position of each direction lives in LDS,
-        // advanced after every round by lane lg for directions lg, lg + G, ... (LDS
-        // operations of one wave are done in order, so the round's reads see the old
-        // value)
-        for (int q = lg; q < 9; q += G) {
-            int32_t bv = 0;
-#pragma unroll
-            for (int i = 0; i < 9; ++i) bv = q == i ? bst[i] : bv;
-            s_next[grp][q] = bv;
-        }
-        const int last = lane - lg + G - 1;
-        for (int32_t j0 = b; j0 < e; j0 += G * KR) {
-            int32_t kk[KR];
-            if (j0 == b) {
-#pragma unroll
-                for (int u = 0; u < KR; ++u) kk[u] = kfirst[u];   // ncell beyond e: no direction
-            } else {
-#pragma unroll
-                for (int u = 0; u < KR; ++u) {
-                    const int32_t j = j0 + u * G + lg;
-                    kk[u] = j < e ? key[j] : -1;
-                }
+                for (int i = 0; i < 9; ++i) cnt_d = q == i ? t[i] : cnt_d;
+                if (cnt_d > 0) atomicAdd(&cnt[cell + (q / 3 - 1) * nx + (q % 3 - 1)], cnt_d);
             }
-#pragma unroll
-            for (int u = 0; u < KR; ++u) {
-                if (j0 + u * G >= e) break;   // group-uniform
-                const int32_t k = kk[u];
-                int d = -1;
-                if (k >= 0 && k < ncell) d = near_dir(k, rs, cx, nx);
-                const int dw = d < 0 ? 3 : d / 3, dsh = 10 * (d - 3 * dw);
-                const uint32_t w0 = dw == 0 ? 1u << dsh : 0u, w1 = dw == 1 ? 1u << dsh : 0u,
-                               w2 = dw == 2 ? 1u << dsh : 0u;
-                const uint32_t i0 = group_incl_scan<G>(w0, lg), i1 = group_incl_scan<G>(w1, lg),
-                               i2 = group_incl_scan<G>(w2, lg);
-                if (d >= 0) {
-                    const uint32_t ex = dw == 0 ? i0 - w0 : (dw == 1 ? i1 - w1 : i2 - w2);
-                    bidx[b + s_next[grp][d] + (int32_t)((ex >> dsh) & 1023u)] = j0 + u * G + lg;
-                }
-                const uint32_t t0 = __shfl(i0, last, 64), t1 = __shfl(i1, last, 64),
-                               t2 = __shfl(i2, last, 64);
-                for (int q = lg; q < 9; q += G) {
-                    const int tw = q / 3;
-                    const uint32_t tv = tw == 0 ? t0 : (tw == 1 ? t1 : t2);
-                    s_next[grp][q] += (int32_t)((tv >> (10 * (q - 3 * tw))) & 1023u);
-                }
-            }
-        }
     }
+    // second pass: source indices into the buckets, in source order
+    auto place = [&](auto put) __attribute__((always_inline)) {
+        for (int32_t r = 0; __any(r < mine); r += 4) {
+            uint32_t quad = 0;
+            if (r < 16) {
+                quad = (uint32_t)(kept >> (4 * r));
+            } else {
+                const Keys q = load4(r);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) quad |= direction(q.k[u]) << (4 * u);
+            }
+            int32_t p[4];
+            uint32_t d[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                d[u] = (quad >> (4 * u)) & 15u;
+                p[u] = lds_inc(&pos[d[u]][lane]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) put(d[u] != NONE, p[u], j0 + r + u);
+        }
+    };
+    if (staged) {
+        place([&](bool near, int32_t p, int32_t j) { stage[near ? p : RC_STAGE] = (uint16_t)(j - wb); });
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int32_t i = lane; i < we - wb; i += 64) bidx[wb + i] = wb + stage[i];
+    } else {
+        place([&](bool near, int32_t p, int32_t j) {
+            if (near) bidx[p] = j;
+        });
+    }
+    if (!__syncthreads_or(nfar)) return;
     int32_t tot;
-    const int32_t pre = wg_excl_scan<BIN_BLOCK>(nfar, sh, tot);
-    if (tot == 0) return;                      // block-uniform
+    const int32_t pre = wg_excl_scan<BLK>(nfar, sh, tot);
     if (threadIdx.x == 0) s_base = atomicAdd(farn, tot);
     __syncthreads();
     if (nfar == 0) return;
     int64_t slot = (int64_t)s_base + pre;
-    for (int32_t j = b + lg; j < e; j += G) {
+    // of the first sixteen only those without a direction are read again
+    const uint64_t ones = 0x1111111111111111ull;
+    uint64_t x = kept ^ (ones * NONE);
+    x = ~(x | x >> 1 | x >> 2 | x >> 3) & ones;   // bit 4 u: no direction
+    if (mine < 16) x &= (1ull << (4 * mine)) - 1;
+    for (int32_t r = 16;;) {
+        int32_t j;
+        if (x) {
+            j = j0 + (__ffsll((unsigned long long)x) - 1) / 4;
+            x &= x - 1;
+        } else {
+            if (r >= mine) break;
+            j = j0 + r++;
+        }
         const int32_t k = key[j];
-        if (k < 0 || k >= ncell || near_dir(k, rs, cx, nx) >= 0) continue;
-        far_put(k, j, slot++, cap, flist, cnt, fcnt);
+        if ((uint32_t)k < (uint32_t)ncell && direction(k) == NONE) far_put(k, j, slot++, cap, flist, cnt, fcnt);
     }
 }
 
@@ -1198,13 +1231,18 @@ static void rebin_count_launch(fp_ctx* c, const fp_particles* src, const int32_t
     const int32_t nc = c->ncell;
     int32_t nx, ny;
     rebin_grid(c, nx, ny);
-    const int32_t cblocks = (int32_t)(((int64_t)nc * G + BIN_BLOCK - 1) / BIN_BLOCK);
     // cnt, ccnt (far counts), ccur and farn are zero on entry: the previous sort call left
     // them so
-    hipLaunchKernelGGL((rebin_count_kernel<G>), dim3(cblocks + FAR_BLOCKS), dim3(BIN_BLOCK), 0, s, nc,
-                       nx, src->n, (const int64_t*)src->n_dev, c->cfg.capacity, cblocks, src_off,
-                       (const int32_t*)src->key,
-                       c->ncnt, c->bidx, c->cnt, c->ccnt, c->farn, c->cmask, c->errcount);
+    auto launch = [&](auto block) {
+        constexpr int BLK = decltype(block)::value;
+        const int32_t cblocks = (int32_t)(((int64_t)nc * G + BLK - 1) / BLK);
+        hipLaunchKernelGGL((rebin_count_kernel<G, BLK>), dim3(cblocks + FAR_BLOCKS), dim3(BLK), 0, s, nc,
+                           nx, src->n, (const int64_t*)src->n_dev, c->cfg.capacity, cblocks, src_off,
+                           (const int32_t*)src->key, c->ncnt, c->bidx, c->cnt, c->ccnt, c->farn, c->cmask,
+                           c->errcount);
+    };
+    if ((int64_t)nc * G > RC_SMALL) launch(std::integral_constant<int, 1024>{});
+    else launch(std::integral_constant<int, 256>{});
 }
 
 // pass 2 with G lanes per destination cell
