@@ -1164,6 +1164,12 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 && G >= 32 ? 4 : 1) void rebin_
                 s1 += (double)kvy[u];
                 s2 += (double)kvz[u];
             }
+        // the partial sum of the slots q = lg modulo G back to lane lg: the reduction's order,
+        // and so its bits, do not depend on the shift (here, and for the moments in mom_finish)
+        const int from = (lg + off) & (G - 1);
+        s0 = __shfl(s0, from, G);
+        s1 = __shfl(s1, from, G);
+        s2 = __shfl(s2, from, G);
     } else {
         for (int32_t q = lg; q < ncnt; q += G) {
             s0 += (double)r.dvx[base + q];
@@ -1190,7 +1196,8 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 && G >= 32 ? 4 : 1) void rebin_
                            (double)ld_off(r.dvz, base + q) - U2, acc);
     }
     mom_finish<BLK, G, NVX>(sm, acc, grp, lg, in, ncnt, U0, U1, U2,
-                             mom + (int64_t)(in ? k : 0) * MOM);
+                            mom + (int64_t)(in ? k : 0) * MOM,
+                            grp * G + (regs ? (lg - off) & (G - 1) : lg));
     if (samp_cell && lg < 14) {
         // the lane's time-average sums from the record's entries, rebuilt from the final
         // sums in LDS (the values mom_finish stored) instead of reading the record back;

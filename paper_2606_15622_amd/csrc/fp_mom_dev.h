@@ -77,16 +77,17 @@ __device__ __forceinline__ double mom_entry(const MomShared<BLOCK, G>& sm, int g
 // add half of the partials and one lane exchange joins the halves: chains of G/2 instead
 // of G dependent adds), then the record of the cell, one entry per lane:
 // N, U, theta, P, T, R, W, H (moments / N; R, W, H zero when only NV_LOW values were
-// accumulated), pad.  Every thread of the block must call.
+// accumulated), pad.  slot: the thread whose place in that order the partials take, its own or
+// a rotation of the group's.  Every thread of the block must call.
 template <int BLOCK, int G, int NVX = NV>
 __device__ __forceinline__ void mom_finish(MomShared<BLOCK, G>& sm, const double (&acc)[NVX], int grp,
                                            int lg, bool in, int32_t n, double U0, double U1,
-                                           double U2, double* __restrict__ rec) {
+                                           double U2, double* __restrict__ rec, int slot) {
 #pragma unroll
     for (int r0 = 0; r0 < NVX; r0 += MR) {
 #pragma unroll
         for (int v = 0; v < MR; ++v)
-            if (r0 + v < NVX) sm.red[v][threadIdx.x] = acc[r0 + v];
+            if (r0 + v < NVX) sm.red[v][slot] = acc[r0 + v];
         __syncthreads();
         if constexpr (G >= 32) {
             constexpr int H = G / 2;   // stripe width, at least MR

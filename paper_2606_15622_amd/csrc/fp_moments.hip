@@ -82,7 +82,8 @@ __global__ __launch_bounds__(MOM_BLOCK) void moments_kernel(
         mom_accum<NVX>((double)vx[b + j] - U0, (double)vy[b + j] - U1, (double)vz[b + j] - U2, acc);
     __shared__ MomShared<MOM_BLOCK, G> sm;
     const int grp = (int)(threadIdx.x / G);
-    mom_finish<MOM_BLOCK, G, NVX>(sm, acc, grp, lg, in, n, U0, U1, U2, mom + (int64_t)(in ? cell : 0) * MOM);
+    mom_finish<MOM_BLOCK, G, NVX>(sm, acc, grp, lg, in, n, U0, U1, U2, mom + (int64_t)(in ? cell : 0) * MOM,
+                                   threadIdx.x);
     if (in && (samp0 || samp1)) {
         // every term with a compile-time entry index (no indexed access to m), the lane's
         // own ones kept
