@@ -11,6 +11,8 @@
 #include "fp_mom_dev.h"
 #include "fp_sample_dev.h"
 
+#include <type_traits>
+
 namespace fpg {
 
 // one-wave workgroups: the moment reduction's LDS (MomShared) then takes 7 KB per wave
@@ -45,25 +47,53 @@ __global__ __launch_bounds__(MOM_BLOCK) void moments_kernel(
         sv0[u] = in && samp0 && e < 14 ? samp0[at] : 0.0;
         sv1[u] = in && samp1 && e < 14 ? samp1[at] : 0.0;
     }
+    // all loads first: summed where they are loaded, every one would be waited for before the
+    // next goes out (1e4 cells of 255 FP64 particles 26 -> 18.5 us)
     T cx[K], cy[K], cz[K];
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int32_t j = lg + k * G;
+        cx[k] = cy[k] = cz[k] = (T)0;
         if (j < n) {
-            cx[k] = vx[b + j];
-            cy[k] = vy[b + j];
-            cz[k] = vz[b + j];
-            s0 += (double)cx[k];
-            s1 += (double)cy[k];
-            s2 += (double)cz[k];
+            cx[k] = ld_off(vx, b + j);
+            cy[k] = ld_off(vy, b + j);
+            cz[k] = ld_off(vz, b + j);
         }
     }
-    for (int32_t j = lg + K * G; j < n; j += G) {
-        s0 += (double)vx[b + j];
-        s1 += (double)vy[b + j];
-        s2 += (double)vz[b + j];
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {   // (the sums are never -0, so the zeros change nothing)
+        s0 += (double)cx[k];
+        s1 += (double)cy[k];
+        s2 += (double)cz[k];
+        // kept in their own type, widened again below: the wide copies would cost a wave
+        if (sizeof(T) == 4) __asm__ volatile("" : "+v"(cx[k]), "+v"(cy[k]), "+v"(cz[k]));
     }
+    // particles beyond the cache, KT per lane at a time: the leaves of a tree are ragged (9e6
+    // particles on 614 000 leaves: mean 15, an eighth of them 50 to 100, at four lanes each) and
+    // a wave takes as long as its largest cell (that case 232 -> 212 us; eight lanes would take
+    // 137, but sum in another order, whose last bits ill-conditioned leaves blow up)
+    auto beyond = [&](auto at_a_time, auto add) __attribute__((always_inline)) {
+        constexpr int KT = decltype(at_a_time)::value;
+        for (int32_t j0 = lg + K * G; j0 < n; j0 += KT * G) {
+            T tx[KT], ty[KT], tz[KT];
+#pragma unroll
+            for (int k = 0; k < KT; ++k) {
+                const int32_t j = b + min(j0 + k * G, n - 1);
+                tx[k] = ld_off(vx, j);
+                ty[k] = ld_off(vy, j);
+                tz[k] = ld_off(vz, j);
+            }
+#pragma unroll
+            for (int k = 0; k < KT; ++k)
+                if (j0 + k * G < n) add((double)tx[k], (double)ty[k], (double)tz[k]);
+        }
+    };
+    beyond(std::integral_constant<int, 8>{}, [&](double x, double y, double z) {
+        s0 += x;
+        s1 += y;
+        s2 += z;
+    });
     s0 = group_sum<G>(s0);
     s1 = group_sum<G>(s1);
     s2 = group_sum<G>(s2);
@@ -78,8 +108,8 @@ __global__ __launch_bounds__(MOM_BLOCK) void moments_kernel(
         const int32_t j = lg + k * G;
         if (j < n) mom_accum<NVX>((double)cx[k] - U0, (double)cy[k] - U1, (double)cz[k] - U2, acc);
     }
-    for (int32_t j = lg + K * G; j < n; j += G)
-        mom_accum<NVX>((double)vx[b + j] - U0, (double)vy[b + j] - U1, (double)vz[b + j] - U2, acc);
+    beyond(std::integral_constant<int, 6>{},
+           [&](double x, double y, double z) { mom_accum<NVX>(x - U0, y - U1, z - U2, acc); });
     __shared__ MomShared<MOM_BLOCK, G> sm;
     const int grp = (int)(threadIdx.x / G);
     mom_finish<MOM_BLOCK, G, NVX>(sm, acc, grp, lg, in, n, U0, U1, U2, mom + (int64_t)(in ? cell : 0) * MOM,
