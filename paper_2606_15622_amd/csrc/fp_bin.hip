@@ -358,22 +358,11 @@ static void gather_dispatch(fp_ctx* c, const fp_particles* src, fp_particles* ds
 // the old cell's own index range ("buckets": bidx, bucket ends in bend[cell][9]); every
 // other particle (moved farther, or after the grouped range) goes to a short far list.
 // Every old cell adds its bucket lengths to the counts of the destinations (nine integer
-// atomics), far arrivals add one each, and one scan gives the offsets.  Pass 2 (one group per DESTINATION cell)
-// concatenates its nine buckets in the order of their old cells -- which is the order of
-// source indices, i.e. the stable order -- inserting each far arrival before the buckets
-// whose old cell starts after it, and writes its slots contiguously (whole cache lines,
-// each written once).  The only global atomics are those of the far list.
-
-// direction 0..8 of key k among the 3 x 3 cells around the old cell (column cx, its row
-// starting at cell rs), -1 for any other cell; no division: k's row is told by comparing
-// k - rs with 0 and nx
-__device__ __forceinline__ int near_dir(int32_t k, int32_t rs, int32_t cx, int32_t nx) {
-    const int32_t rel = k - rs;
-    const int32_t dy = rel < 0 ? -1 : (rel >= nx ? 1 : 0);
-    const int32_t dx = rel - dy * nx - cx;
-    if (rel < -nx || rel >= 2 * nx || dx < -1 || dx > 1) return -1;
-    return (dy + 1) * 3 + (dx + 1);
-}
+// atomics), far arrivals add one each, and one scan gives the offsets.  Pass 2 (one group
+// per DESTINATION cell) concatenates its nine buckets in the order of their old cells --
+// which is the order of source indices, i.e. the stable order -- inserting each far arrival
+// before the buckets whose old cell starts after it, and writes its slots contiguously
+// (whole cache lines, each written once).
 
 // inclusive prefix sum over the G consecutive lanes of a group (lane lg of it): steps
 // inside rows of 16 lanes by DPP row shifts (lanes before the row start read 0, lanes
@@ -562,7 +551,9 @@ __global__ __launch_bounds__(BLK) void rebin_count_kernel(
         }
         return q;
     };
-    // direction of a key, NONE for a far, deleted or invalid one
+    // direction 0..8 of key k among the 3 x 3 cells around the old cell (column cx, its row
+    // starting at cell rs), NONE for any other, deleted or invalid one; no division: k's row is
+    // told by comparing k - rs with 0 and nx, and no branch
     constexpr uint32_t NONE = 9;
     auto direction = [&](int32_t k) __attribute__((always_inline)) {
         const int32_t rel = k - rs;

@@ -1,14 +1,15 @@
 // fp_lite.hip -- the paper's LITE surrogate on MFMA: 16 low-order inputs -> 256 -> 256 ->
 // 256 -> 256 (ReLU) -> 9 (Secs. "Phase 1-2", "Neural Network Architecture", "Phase 3").
 //
-// Inference is one kernel: every wave keeps 32 cells (the MFMA columns) in registers
-// through all five layers, and the workgroup stages one layer's BF16 weights at a time
-// through LDS (the 408 KB of weights do not fit in LDS together; a 256 x 256 layer is
-// 128 KB).  The activations never leave the registers: the columns of every next-layer
-// weight matrix are permuted so that the rows a lane holds after one layer are exactly
-// the k-slots it feeds into the next (the permutation of fp_nn.hip, over 16 k-steps).
-// Training runs layer by layer over batches in HBM (MFMA forward, backward and split-K
-// weight gradients, fixed-order reductions: bitwise reproducible) with Adam on FP32
+// Inference is one persistent kernel: every wave keeps 32 cells (the MFMA columns) in
+// registers through all five layers, from the moment record to the update record, and the
+// workgroup streams the BF16 weights through LDS (the 408 KB do not fit in LDS together; a
+// 256 x 256 layer is 128 KB).  The activations never leave the registers: the columns of
+// every next-layer weight matrix are permuted so that the rows a lane holds after one layer
+// are exactly the k-slots it feeds into the next (the permutation of fp_nn.hip, over 16
+// k-steps).  Training is a kernel for the chain of a batch tile (forward, loss and backward,
+// activations kept on the CU), one for the weight gradients (split-K MFMA) and one that
+// reduces them in a fixed order (bitwise reproducible) and takes the Adam step on FP32
 // master weights.
 //
 // Inputs (solver units, then standardised): rho, T, U (3), Pi (11 12 13 22 23 33), q (3),

@@ -640,8 +640,13 @@ static void collide_dispatch(fp_ctx* c, fp_particles* p, const int32_t* off, con
                              const double* rec, uint32_t step, int move, const uint32_t* sp,
                              uint32_t* adv, hipStream_t s) {
     // about two particles per lane: at 100 particles per cell a whole wave per cell (its
-    // coefficients wave-uniform, in scalar registers; 74 VGPRs, 6 waves per SIMD) was
-    // measured 4 % faster than 32 lanes (82 VGPRs, 5 waves) and 9 % faster than 16
+    // coefficients wave-uniform, in scalar registers; 72 VGPRs, 7 waves per SIMD) was
+    // measured 4 % faster than 32 lanes (80 VGPRs, 6 waves) and 9 % faster than 16.  The
+    // kernel is bound by VALU issue (0.77 of it at 2e7 particles): three-input logic in
+    // Philox, one 32-bit offset per element for all arrays, four group sums in one exchange,
+    // reciprocal cell sizes as arguments and a straight flight decided by its end point took
+    // it from 282 to 259 us there and from 512 to 472 us on 1.8e7 particles of a quadtree
+    // (two lanes fewer per cell, 16 for 32, would give the tree another 0.8 %)
     switch (lanes_per_cell(c, p->n, FILL_4, 2)) {
         case 4: collide_launch<T, 4, GEOM>(c, p, off, mom, rec, step, move, sp, adv, s); break;
         case 8: collide_launch<T, 8, GEOM>(c, p, off, mom, rec, step, move, sp, adv, s); break;
