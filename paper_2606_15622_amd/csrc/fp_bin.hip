@@ -482,7 +482,7 @@ __global__ __launch_bounds__(BLK) void rebin_count_kernel(
     __shared__ int32_t sh[BLK / 64];
     __shared__ int32_t s_base;
     __shared__ int32_t s_pos[BLK / 64][10][64];   // the last row: no direction
-    __shared__ uint16_t s_stage[BLK / 64][RC_STAGE + 2];
+    __shared__ __attribute__((aligned(16))) uint16_t s_stage[BLK / 64][RC_STAGE + 8];   // (and a place for no bucket)
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
     if ((int32_t)blockIdx.x >= cell_blocks) {
@@ -533,6 +533,11 @@ __global__ __launch_bounds__(BLK) void rebin_count_kernel(
     const bool staged = we >= wb && we - wb <= RC_STAGE && __all(cell >= ncell || (b >= wb && b <= e && e <= we));
 #pragma unroll
     for (int i = 0; i < 9; ++i) pos[i][lane] = 0;
+    // all of the range is written out, also behind a cell's buckets, where no particle with a
+    // direction puts anything; with a bad src_off the ranges of different waves overlap, and
+    // what a gather reads there must be a particle's index: wb then
+#pragma unroll
+    for (int i = 0; i < RC_STAGE / 512; ++i) reinterpret_cast<uint4*>(stage)[i * 64 + lane] = make_uint4(0, 0, 0, 0);
     // four keys of the run from r on, ncell (no destination) beyond it.  Read as one, up to
     // three keys past the run, but for the last waves
     struct Keys { int32_t k[4]; };
@@ -637,6 +642,8 @@ __global__ __launch_bounds__(BLK) void rebin_count_kernel(
         }
     };
     if (staged) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         place([&](bool near, int32_t p, int32_t j) { stage[near ? p : RC_STAGE] = (uint16_t)(j - wb); });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
