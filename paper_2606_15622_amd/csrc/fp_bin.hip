@@ -514,15 +514,16 @@ __global__ __launch_bounds__(BLK) void rebin_count_kernel(
     const int lg = (int)(gt % G);
     int32_t nfar = 0, b = 0, e = 0, cx = 0, rs = 0;
     if (cell < ncell) {
-        b = max(src_off[cell], 0);
+        b = (int32_t)min((int64_t)max(src_off[cell], 0), n);
         e = (int32_t)min((int64_t)src_off[cell + 1], n);
         cx = cell % nx;
         rs = cell - cx;
     }
     // lane lg takes the lg-th run of the cell's particles, so that a particle's rank among
     // those of its direction is the count of the lanes before plus its lane's own so far
-    const int32_t chunk = (max(e - b, 0) + G - 1) / G, j0 = b + lg * chunk;
-    const int32_t mine = max(min(e - j0, chunk), 0);
+    const int32_t size = e > b ? e - b : 0;   // (a bad src_off may leave any e)
+    const int32_t chunk = (size + G - 1) / G, j0 = b + lg * chunk;
+    const int32_t mine = max(min(size - lg * chunk, chunk), 0);
     int32_t(&pos)[10][64] = s_pos[threadIdx.x >> 6];   // this lane's column only
     uint16_t* stage = s_stage[threadIdx.x >> 6];
     // the wave's cells follow each other, so do their ranges of bidx: they are put together in
@@ -561,7 +562,7 @@ __global__ __launch_bounds__(BLK) void rebin_count_kernel(
     // told by comparing k - rs with 0 and nx, and no branch
     constexpr uint32_t NONE = 9;
     auto direction = [&](int32_t k) __attribute__((always_inline)) {
-        const int32_t rel = k - rs;
+        const int32_t rel = (int32_t)((uint32_t)k - (uint32_t)rs);   // (an invalid key may be anything)
         const int32_t dy = (rel >= nx ? 1 : 0) - (rel < 0 ? 1 : 0);
         const int32_t dx = rel - dy * nx - cx;
         const bool near = (uint32_t)k < (uint32_t)ncell & rel >= -nx & rel < 2 * nx & (uint32_t)(dx + 1) < 3u;

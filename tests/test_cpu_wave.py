@@ -19,7 +19,7 @@ def build(tmp_path_factory):
     def make(name):
         if name not in done:
             done[name] = str(out / name)
-            subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O2", "-fwrapv", "-ffp-contract=off", "-w",
+            subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O2", "-ftrapv", "-ffp-contract=off", "-w",
                             "-I", os.path.join(HERE, "cpu_wave"), "-I", CSRC,
                             os.path.join(HERE, "cpu_wave", name + ".cpp"), "-o", done[name]], check=True)
         return done[name]
@@ -31,7 +31,8 @@ def run(program, *args):
     assert r.returncode == 0, (r.returncode, r.stderr)
 
 
-# offsets as the contract has them; some decreasing; some beyond the particles; some negative
-@pytest.mark.parametrize("kind", [0, 1, 2, 3])
+# offsets as the contract has them; some decreasing; some beyond the particles; some negative; some
+# at the ends of the 32-bit range (signed overflows trap; so do those of invalid keys)
+@pytest.mark.parametrize("kind", [0, 1, 2, 3, 4])
 def test_source_indices_of_the_resort(build, kind):
     run(build("rebin_count"), kind)
