@@ -501,10 +501,12 @@ __global__ __launch_bounds__(512) void lite_train_kernel(int64_t B, const float*
         auto put_out = [&](auto inner, const float (&v)[16], __bf16* hs, int ct, int f) {
             put_tile<decltype(inner)::value>(hs, S::SH, sm.tr[rt] - rt * 32 * S::SP - ct * 32, S::SP, ct * 32 + c, rt * 32, h,
                                              v);
+            lds_wave_barrier();   // other lanes' values come back
 #pragma unroll
             for (int s = 0; s < 2; ++s)
                 *(bf16x8*)(sf + (((int64_t)(f + rt) * groups + g0 + 2 * ct + s) * 64 + lane) * 8) =
                     *(const bf16x8*)(sm.tr[rt] + c * S::SP + 16 * s + 8 * h);
+            lds_wave_barrier();   // before the next tile takes their place
         };
         // products of the wave's units with the tile's samples; M fragments from nf on (a later
         // layer's weights) are loaded into nw in between, one per k-step: issued together, 128

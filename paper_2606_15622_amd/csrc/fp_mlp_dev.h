@@ -29,6 +29,14 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// the same within a wave, for data that its lanes exchange through LDS: nothing to wait for (a
+// wave's LDS operations are done in order), but the compiler keeps the order too
+__device__ __forceinline__ void lds_wave_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // the lane's 16 values of a 32 x 32 output tile (rows = units r0 .., columns = samples), as
 // bfloat16, into the sample-major image s[sample][unit] (the next product's B operand; only
 // with SAMPLE_MAJOR) and the unit-major image t[unit][sample] (the operands of the weight gradients,

@@ -28,6 +28,9 @@
 #define __shared__ static __attribute__((section("lds")))
 #define hipLaunchKernelGGL(...) ((void)0)   // launched by the tests themselves (emu::launch)
 
+#define amdgpu_waves_per_eu(...) unused
+
+using std::isfinite;
 using std::max;
 using std::min;
 
