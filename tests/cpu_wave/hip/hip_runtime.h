@@ -51,9 +51,19 @@ inline double2 make_double2(double a, double b) { return {a, b}; }
 typedef void* hipStream_t;
 typedef int hipError_t;
 constexpr int hipSuccess = 0, hipMemcpyDeviceToDevice = 3;
-inline int hipMalloc(void**, size_t) { abort(); }
-inline int hipFree(void*) { abort(); }
-inline int hipDeviceSynchronize() { abort(); }
+#define HIP_SYMBOL(x) (x)
+#define EMU_HOST_CALL(name)   \
+    template <typename... A>  \
+    int name(A&&...) {        \
+        abort();              \
+    }
+EMU_HOST_CALL(hipMalloc)
+EMU_HOST_CALL(hipFree)
+EMU_HOST_CALL(hipDeviceSynchronize)
+EMU_HOST_CALL(hipGetDevice)
+EMU_HOST_CALL(hipSetDevice)
+EMU_HOST_CALL(hipGetSymbolAddress)
+EMU_HOST_CALL(hipMemcpyAsync)
 inline int hipGetLastError() { return 0; }
 
 extern char __start_lds[], __stop_lds[];

@@ -46,3 +46,7 @@ def test_source_indices_of_the_resort(build, kind):
 
 def test_chain_of_the_lite_training(build):
     run(build("lite_train"))
+
+
+def test_training_of_the_network(build):
+    run(build("nn_train"))
