@@ -434,8 +434,8 @@ __device__ __forceinline__ int32_t bucket_len(const int32_t* __restrict__ bend, 
 // Far movers are appended to the list with one atomic per block (cells) or per wave
 // (tail) on its length.  These atomics on one address are what bounds the kernel as soon as
 // most blocks have a far mover: 10.6 ns each, whatever else runs, 66 us for the 6272 blocks of
-// 256 threads that 2e7 particles on 200 704 cells make.  Hence blocks of 1024 threads for more
-// than RC_SMALL lanes (93 -> 67 us; 1e6 particles on 1e4 cells 14.5 -> 11; the grid of 100
+// 256 threads that 2e7 particles on 200 704 cells make.  Hence blocks of 1024 threads from
+// RC_WIDE lanes on (93 -> 67 us; 1e6 particles on 1e4 cells 14.5 -> 11; the grid of 100
 // cells, 25 narrow blocks or 7 wide ones, 5.6 against 7.9 us the other way).  Persistent blocks
 // that collect far movers in LDS over several tiles: 69 and 13 us.
 // A lane takes a run of consecutive particles, and LDS counters of its own give a particle
@@ -464,8 +464,12 @@ __device__ __forceinline__ int32_t strip_cell(int32_t t, int32_t nx, int32_t ny)
 
 // entries of bidx that a wave of the count kernel puts together in LDS
 constexpr int RC_STAGE = 1024;
-// lanes up to which workgroups of 256 are taken (up to 512 of them)
-constexpr int64_t RC_SMALL = 512 * 256;
+// lanes from which workgroups of 1024 are taken: enough of them for most CUs.  Whole re-sorts of
+// 100 particles per cell, narrow against wide, FP32 (FP64): 10^2 cells 18.2 / 19.1 us, 46^2
+// (135 424 lanes) 23.1 / 23.5 (24.5 / 25.2), 56^2 (200 704) 25.6 / 25.7 (28.6 / 28.9), 58^2 (215 296)
+// 25.7 / 25.7 (30.0 / 29.4), 64^2 27.6 / 27.5 (32.1 / 31.7), 80^2 35.6 / 34.4, 110^2 50.2 / 45.5,
+// 200^2 122.7 / 117.6
+constexpr int64_t RC_WIDE = 200 * 1024;
 // *p += 1 in LDS, old value returned
 __device__ __forceinline__ int32_t lds_inc(int32_t* p) {
     return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -1247,7 +1251,7 @@ static void rebin_count_launch(fp_ctx* c, const fp_particles* src, const int32_t
                            (const int32_t*)src->key, c->ncnt, c->bidx, c->cnt, c->ccnt, c->farn, c->cmask,
                            c->errcount);
     };
-    if ((int64_t)nc * G > RC_SMALL) launch(std::integral_constant<int, 1024>{});
+    if ((int64_t)nc * G >= RC_WIDE) launch(std::integral_constant<int, 1024>{});
     else launch(std::integral_constant<int, 256>{});
 }
 
