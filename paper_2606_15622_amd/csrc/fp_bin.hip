@@ -932,7 +932,8 @@ __global__ __launch_bounds__(BIN_BLOCK) void rebin_gather_kernel(
 // moment reduction in LDS) then wait for the wave itself and never for other cells.
 constexpr int GM_BLOCK = 64;
 
-// (in FP64 five positions a lane take 134 registers, one wave fewer per SIMD: bounded to 128)
+// (in FP64 five positions a lane take 134 registers, one wave fewer per SIMD: bounded to 128, of
+// which two are spilled)
 template <typename T, int G, int NVX, int BLK = GM_BLOCK>
 __global__ __launch_bounds__(BLK, sizeof(T) == 8 && G >= 32 ? 4 : 1) void rebin_gather_mom_kernel(
     int32_t ncell, int32_t nx, int32_t ny, int64_t n, const int64_t* __restrict__ n_dev,
@@ -955,7 +956,8 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 && G >= 32 ? 4 : 1) void rebin_
     // far arrivals of a cell staged in LDS, up to FCAP of them (their ranks compare every
     // arrival with all others and with the nine source ranges), in the space of the
     // moment reduction, which is used only after the gather's last barrier: the
-    // workgroup's LDS stays below 32 KB (five workgroups per CU)
+    // workgroup's LDS stays at 7 to 9 KB from 16 lanes on (15 KB at four), so that the 16
+    // one-wave workgroups that a CU's registers allow fit into 160 KB
     constexpr int FCAP = (2048 / GROUPS) < (int)(sizeof(sm.red) / (sizeof(int32_t) * GROUPS))
                              ? (2048 / GROUPS) : (int)(sizeof(sm.red) / (sizeof(int32_t) * GROUPS));
     static_assert(sizeof(int32_t) * GROUPS * FCAP <= sizeof(sm.red), "far staging space");

@@ -137,7 +137,8 @@ __device__ __forceinline__ void cell_inputs(const fp_config& g, const double* __
 // 655 us.  Of a pass of 23 us at full clock the hidden layers take 16 (two thirds of their
 // MFMA rate), the FP64 inputs and records 5, the first layer 1.4.  Four waves of 64 cells
 // (half the LDS reads, twice the registers) were slower (490 to 600 us), and without any
-// fragment reads it would take 445: the LDS is not the bound.
+// fragment reads it would take 445: the LDS is not the bound.  The eight waves fill their 256
+// registers; in mode 2 two of a lane's and 123 scalar ones (to lanes) are spilled.
 constexpr int CH_N = 26, CH_BF = KS * 512;   // chunks of a pass, bfloat16 of a chunk (layer 1: half)
 constexpr int MROW = MOM + 1;   // LDS row of a record: rows start on different banks
 
@@ -943,12 +944,14 @@ extern "C" int fp_lite_load(fp_ctx* c, fp_lite* n, const float* params, hipStrea
     return check_launch(c, "fp_lite_load");
 }
 
-// a workgroup per CU: eight waves (two per SIMD, which hide each other's latencies) once they
-// occupy every CU, else four (twice the workgroups)
+// a workgroup per CU: four waves while their workgroups reach all cells in one pass, else eight
+// (two per SIMD, which hide each other's latencies), also where those leave CUs idle: mode 2 on
+// 4096 / 32,768 / 32,769 / 65,536 / 131,072 cells takes 21.7 / 26.1 / 41.5 / 47.2 / 90.8 us with four and
+// 28.3 / 31.4 / 31.2 / 38.3 / 70.5 us with eight
 template <int MODE>
 static void infer(fp_ctx* c, const fp_lite* n, const double* mom, float* y, double* rec, int32_t* status, double relax,
                   hipStream_t s) {
-    const bool wide = c->ncell > 128 * 256;
+    const bool wide = c->ncell > 128 * 256;   // 256 workgroups of four waves, 32 cells a wave
     const int w = wide ? 8 : 4;
     const int grid = std::min(256, (c->ncell + 32 * w - 1) / (32 * w));
     hipLaunchKernelGGL((wide ? lite_infer_kernel<8, MODE> : lite_infer_kernel<4, MODE>), dim3(grid), dim3(64 * w), 0, s,

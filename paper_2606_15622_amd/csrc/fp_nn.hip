@@ -47,9 +47,10 @@ __device__ __forceinline__ float silu_fast(float z) {
     return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-LOG2E * z));
 }
 // training: a = silu(z) = z / (1 + e^-z) and its derivative d, both from one exponential and
-// one reciprocal.  The quotients take the steps of a correctly rounded division (reciprocal,
-// one Newton step, two residual corrections) without its scaling of extreme operands: the
-// divisor is at least 1, and beyond 2^126 both results are below 1e-35
+// one reciprocal.  The quotients take Markstein's steps to a correctly rounded division (IBM J.
+// Res. Dev. 34, 1990: reciprocal, one Newton step, two residual corrections by fused
+// multiply-adds) without scaling extreme operands: the divisor is at least 1, and beyond 2^126
+// both results are below 1e-35
 __device__ __forceinline__ float quotient(float x, float d, float r) {
     float q = x * r;
     q = __builtin_fmaf(__builtin_fmaf(-d, q, x), r, q);
@@ -465,7 +466,7 @@ struct TrainShared {
 // four waves per 32 samples: wave (ct, rt) computes units 32 rt .. of samples 32 ct .. in
 // every layer.  Activations pass from layer to layer through LDS (sample-major), stay there
 // unit-major for the weight gradients, and the pre-activations' derivatives stay in
-// registers; every wave keeps a tenth (CT = 1) or a twentieth of the weight gradient's 40
+// registers; every wave keeps a quarter (CT = 1) or an eighth of the weight gradient's 40
 // tiles in accumulators over all of its workgroup's tiles, so that no activation and no
 // back-propagated gradient goes to memory.
 // Bound by the vector work of the activations (about 2200 instructions per wave and tile
