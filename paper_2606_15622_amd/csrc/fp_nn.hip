@@ -227,9 +227,8 @@ __global__ __launch_bounds__(NN_BLOCK) void nn_infer_kernel(int32_t ncell, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
     const int32_t ntiles = (ncell + 31) / 32;
     // consecutive tiles go to different workgroups: few tiles spread over the CUs before two
-    // share one (a tile is bound by its own SiLU: 12 k cycles of VALU, most of them exponentials
-    // and reciprocals).  The checked closure of 1000 / 40 000 / 200 704 cells takes 17.4 / 24 /
-    // 57 us; with 16 consecutive tiles to a workgroup it took 28 / 34 / 65.  At 1e6 cells, where
+    // share one (a tile issues 1622 vector instructions, 8.1 k busy cycles, 960 of them for its
+    // SiLU).  The checked closure of 1000 / 40 000 / 200 704 cells takes 17.4 / 24 / 57 us; with 16 consecutive tiles to a workgroup it took 28 / 34 / 65.  At 1e6 cells, where
     // every wave has its 7 or 8 tiles either way, no difference
     for (int32_t tile = blockIdx.x + gridDim.x * wave; tile < ntiles; tile += gridDim.x * (NN_BLOCK / 64)) {
         // the weight fragments are read from LDS inside every tile: keep the compiler from
@@ -469,8 +468,9 @@ struct TrainShared {
 // registers; every wave keeps a quarter (CT = 1) or an eighth of the weight gradient's 40
 // tiles in accumulators over all of its workgroup's tiles, so that no activation and no
 // back-propagated gradient goes to memory.
-// Bound by the vector work of the activations (about 2200 instructions per wave and tile
-// against 66 MFMA) and, for a single tile, by the chain of nine dependent phases.  A kernel
+// Bound by the vector work of the activations (1950 instructions per wave and tile with CT = 2,
+// 0.42 of the kernel's time at 200,000 samples, and 2350 with CT = 1, against 66 MFMA), by the
+// waits at its barriers and, for a single tile, by the chain of nine dependent phases.  A kernel
 // per layer with activations, gradients and FP32 pre-activations in memory, per-lane weight
 // conversions and one thread per bias took 1548 us for an Adam step at batch 4096 and 2658 us
 // at 200,000 (residual loss); this takes 24.5 and 201 us (the kernel itself 21 and 190).
